@@ -82,3 +82,43 @@ def test_quantize_pack_3bit_llama_rows_bit_exact():
     np.testing.assert_array_equal(host_u32(w.q)[rows], Q)
     np.testing.assert_array_equal(host_u16(w.scales)[rows], s.view(np.uint16))
     np.testing.assert_array_equal(host_u16(w.zeros)[rows], z.view(np.uint16))
+
+
+@pytest.mark.parametrize("bits,G,rows,offset", [
+    (4, 32, 1, 0), (4, 96, 5, 0), (4, 256, 37, 1), (4, 512, 37, 0), (4, 1024, 9, 1),   # lanes of a group: 4 .. 64, a wave
+    (3, 32, 3, 1), (3, 96, 4, 0), (3, 512, 5, 0), (3, 640, 2, 1),
+    (2, 64, 1, 1), (2, 192, 7, 0), (2, 512, 3, 0), (2, 1088, 2, 1),
+])
+def test_every_group_width_and_alignment_bit_exact(bits, G, rows, offset):
+    """Group sizes on both kernels, odd row counts, a weight and an output
+    that start 4 bytes past a 16-byte boundary, values next to every tie of
+    the grid (the fp32 decision falls back to fp64 there), infinities'
+    neighbourhood and an empty-range group."""
+    d_in = 4 * G if bits != 3 else 128 * G // np.gcd(128, G)
+    g = np.random.default_rng(G + bits)
+    W = (0.02 * g.standard_normal((rows, d_in))).astype(np.float32)
+    qmax = (1 << bits) - 1
+    step = np.float32(0.0078125)
+    ties = ((np.arange(G) % qmax) - 1.5).astype(np.float32) * step
+    W[0, :G] = np.where(np.arange(G) % 3 == 0, ties, np.nextafter(ties, np.float32(np.inf) * (-1.0) ** np.arange(G)))
+    W[0, 0], W[0, 1] = -2 * step, (qmax - 2) * step
+    W[0, G:2 * G] = 3.0e38 * np.sign(W[0, G:2 * G])
+    W[-1, -G:] = 0.0
+    host = torch.from_numpy(W)
+    buf = torch.empty(W.size + offset, dtype=torch.float32, device="cuda")
+    Wd = buf[offset:].view(rows, d_in)
+    Wd.copy_(host)
+    w = cl.quantize_pack(Wd, bits, G)
+    Q, s, z = quant.quantize_pack(W, bits, G)
+    np.testing.assert_array_equal(host_u32(w.q), Q)
+    np.testing.assert_array_equal(host_u16(w.scales), s.view(np.uint16))
+    np.testing.assert_array_equal(host_u16(w.zeros), z.view(np.uint16))
+    import ctypes
+    out = torch.full((W.size + 2,), 7.0, dtype=torch.float32, device="cuda")
+    qc = w.c()
+    at = out[offset:]
+    assert cl.lib().cl_dequantize(ctypes.byref(qc), ctypes.c_void_p(at.data_ptr()), None) == 0
+    torch.cuda.synchronize()
+    ref = quant.dequant_packed(Q, s, z, bits, G, d_in).astype(np.float32).reshape(-1)
+    np.testing.assert_array_equal(at[:W.size].cpu().numpy(), ref)
+    assert (out[offset + W.size:] == 7.0).all()
