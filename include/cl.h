@@ -135,13 +135,13 @@ cl_status cl_dequantize(const cl_qweight* w, float* W_hat, void* stream);
  *         (output; may be NULL)
  *  ws     device workspace of cl_build_compensation_workspace(...) bytes,
  *         256-byte aligned (fp64 residual, Gram matrix and eigenvectors)
- * Computed in fp64 from the Gram matrix of E over its smaller side with a
- * parallel cyclic Jacobi eigensolver; singular values far below
- * 1e-8 * sigma[0] have absolute accuracy only.  An offline step: the call
- * waits on the stream once per Jacobi sweep and returns when the factors are
- * enqueued.  Limits: min(d_out, d_in) <= 8192, d_out * d_in <= 2^31
- * (CL_EUNSUPPORTED beyond); CL_EUNSUPPORTED also if the eigensolver does not
- * converge in 40 sweeps.
+ * Computed in fp64 from the Gram matrix of E over its smaller side, reduced
+ * to tridiagonal form by Householder reflectors, with eigenvalues by bisection
+ * and the leading r_max vectors by inverse iteration; singular values far
+ * below 1e-8 * sigma[0] have absolute accuracy only.  An offline step: the
+ * call waits on the stream once, after the eigensolver, and returns when the
+ * factors are enqueued.  Limits: min(d_out, d_in) <= 8192, d_out * d_in <=
+ * 2^31 (CL_EUNSUPPORTED beyond).
  */
 cl_status cl_build_compensation(const float* W, const cl_qweight* w, int32_t r_max, uint16_t* A, uint16_t* B,
                                 float* sigma, void* ws, size_t ws_bytes, void* stream);
@@ -150,8 +150,8 @@ cl_status cl_build_compensation(const float* W, const cl_qweight* w, int32_t r_m
 size_t cl_build_compensation_workspace(int32_t d_out, int32_t d_in, int32_t r_max);
 
 /*
- * Jacobi sweeps the calling thread's last cl_build_compensation call ran
- * (including the final sweep without rotations; 0 before any call).  A
+ * Sweeps over the eigenvectors that the calling thread's last
+ * cl_build_compensation call ran (1 for r_max = 0; 0 before any call).  A
  * report of the eigensolver's work, for timing and tuning.
  */
 int32_t cl_build_compensation_sweeps(void);

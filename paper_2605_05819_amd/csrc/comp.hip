@@ -13,19 +13,18 @@
 // each singular pair makes the largest-magnitude entry of the U column
 // positive (first index on ties).
 //
-// Steps (all fp64, one stream, the host waits once per Jacobi sweep):
+// Steps (all fp64, one stream, the host waits once):
 //  1. E = W - s (q - z) elementwise.
 //  2. The Gram matrix over the smaller side, C = E^T E (d_in <= d_out) or
 //     C = E E^T, with a tiled fp64 GEMM (64 x 64 tiles through LDS).
-//  3. Eigen-decomposition C = X diag(lambda) X^T by the parallel cyclic
-//     Jacobi method: a sweep visits every index pair once in n-1 rounds of
-//     n/2 disjoint pairs (round-robin order); per round one kernel computes
-//     the n/2 rotations that zero C[p][q] and one applies them all at once,
-//     C <- J^T C J (each thread owns a 2 x 2 block, so the update is in place)
-//     and X <- X J.  Pairs with |C[p][q]| below 1e-14 trace(C)/n are skipped;
-//     a sweep with no rotation ends the iteration.
-//  4. sigma = sqrt(lambda) sorted descending; the top r_max eigenvectors are
-//     gathered.  If X holds right vectors V: A = sqrt(sigma) V^T and
+//  3. Eigen-decomposition C = X diag(lambda) X^T, X for the leading r_max only:
+//     Householder reduction to tridiagonal T = Q^T C Q, one launch per
+//     reflector; every eigenvalue of T by bisection on Sturm counts, 64
+//     points of an interval per wave and round; eigenvectors of T by inverse
+//     iteration, one lane per vector, with the vectors of close eigenvalues
+//     orthogonalised among each other; X = Q Z.
+//  4. sigma = sqrt(lambda), descending.  If X holds right vectors V:
+//     A = sqrt(sigma) V^T and
 //     B = E V / sqrt(sigma) (= U sqrt(sigma)); if it holds left vectors U:
 //     B = U sqrt(sigma) and A = U^T E / sqrt(sigma).
 //  5. Sign fix on the U column, rounding to fp16 (one rounding from fp64).
@@ -34,6 +33,8 @@
 // sqrt(eps) * sigma_max carry absolute, not relative, accuracy.  The factors
 // only use the leading ones.
 
+#include <type_traits>
+
 #include "cl_device.h"
 #include "cl_internal.h"
 
@@ -41,29 +42,38 @@ namespace cl {
 
 namespace {
 
-constexpr int kMaxSweeps = 40;
-constexpr double kJacobiTol = 1e-14;
+// Sweep 1 leaves |T| eps / gap of the neighbours in a vector, sweep 2 its square
+// (an unlucky start vector included).
+constexpr int kInverseSweeps = 2;
+// Bisection rounds: 65-section of an interval of width 2 |T| down to 2^-53 |T|.
+constexpr int kSections = 9;
+// Eigenvalues closer than this (relative to |T|) have their vectors
+// orthogonalised; beyond it inverse iteration alone leaves them orthogonal to
+// better than 1e-9, far below the rounding of the fp16 factors.
+constexpr double kCluster = 1e-6;
 
 size_t up256(size_t n) { return (n + 255) / 256 * 256; }
 
 struct CompLayout {
-    size_t E, C, X, rot, lam, order, count, delta, sign, Xr, P, total;
+    size_t E, C, V, tau, lam, d, e, de, p, bounds, scale, sign, Xr, P, total;
 };
 
 CompLayout comp_layout(int d_out, int d_in, int r_max) {
     const size_t n = static_cast<size_t>(d_in <= d_out ? d_in : d_out);
-    const size_t N = n + (n & 1);
     const size_t big = static_cast<size_t>(d_in > d_out ? d_in : d_out);
     CompLayout l;
     l.E = 0;
     l.C = l.E + up256(static_cast<size_t>(d_out) * d_in * 8);
-    l.X = l.C + up256(n * n * 8);
-    l.rot = l.X + up256(n * n * 8);
-    l.lam = l.rot + up256(N / 2 * 2 * 8);
-    l.order = l.lam + up256(n * 8);
-    l.count = l.order + up256(n * 4);
-    l.delta = l.count + up256(kMaxSweeps * 4);
-    l.sign = l.delta + 256;
+    l.V = l.C + up256(n * n * 8);
+    l.tau = l.V + up256(n * n * 8);
+    l.lam = l.tau + up256(n * 8);
+    l.d = l.lam + up256(n * 8);
+    l.e = l.d + up256(n * 8);
+    l.de = l.e + up256(n * 8);
+    l.p = l.de + up256(n * 16);
+    l.bounds = l.p + up256(n * 16);
+    l.scale = l.bounds + 256;
+    l.sign = l.scale + up256(static_cast<size_t>(r_max) * 8 + 8);
     l.Xr = l.sign + up256(static_cast<size_t>(r_max) * 8 + 8);
     l.P = l.Xr + up256(static_cast<size_t>(r_max) * n * 8 + 8);
     l.total = l.P + up256(static_cast<size_t>(r_max) * big * 8 + 8);
@@ -149,142 +159,363 @@ __global__ __launch_bounds__(256) void gemm_nt_f64(const double* __restrict__ X,
     }
 }
 
-// X = identity, sweep counters zero, lam[i] = C[i][i]; workgroup 0 then
-// derives the skip threshold from the trace.
-__global__ __launch_bounds__(256) void jacobi_init_kernel(const double* __restrict__ C, double* __restrict__ Xm, int n,
-                                                          int* __restrict__ count, double* __restrict__ delta) {
-    const size_t idx = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
-    const size_t nn = static_cast<size_t>(n) * n;
-    if (idx < nn) Xm[idx] = (idx / n == idx % n) ? 1.0 : 0.0;
-    if (blockIdx.x == 0) {
-        __shared__ double part[256];
-        if (threadIdx.x < kMaxSweeps) count[threadIdx.x] = 0;
-        double t = 0.0;
-        for (int i = threadIdx.x; i < n; i += 256) t += C[static_cast<size_t>(i) * n + i];
-        part[threadIdx.x] = t;
-        __syncthreads();
-        for (int s = 128; s > 0; s >>= 1) {
-            if (threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) *delta = kJacobiTol * part[0] / n;
-    }
+// Sum over the 256 threads of a workgroup, in a fixed order; red: 4 doubles
+// that the previous use has been read out of.
+__device__ __forceinline__ double wave_sum_f64(double v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
 }
 
-// Round r of the round-robin order over N (even) indices: pair 0 is
-// (r, N-1), pair i >= 1 is ((r + i) mod (N-1), (r - i) mod (N-1)).  Over
-// r = 0..N-2 every unordered pair occurs exactly once; within a round the N/2
-// pairs are disjoint.  Index N-1 == n (odd n) is a placeholder.
-__device__ __forceinline__ void round_pair(int N, int r, int i, int& p, int& q) {
-    const int M = N - 1;
-    if (i == 0) { p = r; q = M; return; }
-    p = (r + i) % M;
-    q = (r - i + M) % M;
+__device__ __forceinline__ double block_sum_f64(double v, double* red) {
+    v = wave_sum_f64(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// One rotation per pair: zero C[p][q] with J = [[c, s], [-s, c]] on (p, q):
-// tau = (C_qq - C_pp) / (2 C_pq), t the smaller root of t^2 + 2 tau t - 1 = 0,
-// c = 1 / sqrt(1 + t^2), s = t c  (the symmetric Schur decomposition of the
-// 2 x 2 block).
-__global__ __launch_bounds__(256) void jacobi_rot_kernel(const double* __restrict__ C, int n, int N, int r,
-                                                         const double* __restrict__ delta, double2* __restrict__ rot,
-                                                         int* __restrict__ count) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    bool did = false;
-    if (i < N / 2) {
-        int p, q;
-        round_pair(N, r, i, p, q);
-        double c = 1.0, s = 0.0;
-        if (p < n && q < n) {
-            const double apq = C[static_cast<size_t>(p) * n + q];
-            if (fabs(apq) > *delta) {
-                const double app = C[static_cast<size_t>(p) * n + p];
-                const double aqq = C[static_cast<size_t>(q) * n + q];
-                const double tau = (aqq - app) / (2.0 * apq);
-                double t;
-                if (fabs(tau) > 1e150) t = 0.5 / tau;
-                else t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                c = 1.0 / sqrt(1.0 + t * t);
-                s = t * c;
-                did = s != 0.0;
+// 1 / q to about an ulp: the hardware estimate and two Newton steps.
+__device__ __forceinline__ double recip_f64(double q) {
+    double r = __builtin_amdgcn_rcp(q);
+    r = fma(r, fma(-q, r, 1.0), r);
+    return fma(r, fma(-q, r, 1.0), r);
+}
+
+// Step k of the Householder reduction, one launch per step.  On entry the
+// rows and columns >= k of C still miss step k - 1's update
+// C -= v w^T + w v^T, w = tau p - (tau^2 / 2)(p . v) v, where p = C v came out
+// of the launch before.  Every workgroup forms w, the updated row k and from
+// it the next reflector (v_k+1 = 1, tail scaled) for itself; then it updates
+// its rows and multiplies each by the new v on the way, so C is read and
+// written once per step.  A thread owns the same CPT columns throughout (v, w
+// and the new v stay in its registers) and R rows at a time; the first R
+// rows' loads are issued before the reductions.  Row i always belongs to
+// workgroup i mod grid.  Bound by the chain of one launch (two reductions; 4.4
+// us a step at <= 256 columns, 7.2 at 1024) up to n ~ 2000, beyond by the 16
+// n^2 bytes.  The whole call at 1024 x 4096, r_max 128: 134 -> 8.6 ms, 4096 x
+// 4096: 4.9 -> 0.13 s, against cyclic Jacobi (10 to 18 sweeps of n - 1 rounds
+// of two launches over C and X).
+template <int CPT, int R>
+__global__ __launch_bounds__(256) void householder_step_kernel(double* __restrict__ C, int n, int k,
+                                                               double* __restrict__ V,
+                                                               const double* __restrict__ p_in,
+                                                               double* __restrict__ p_out, double* __restrict__ tau,
+                                                               double* __restrict__ d, double* __restrict__ e) {
+    __shared__ double red[2][4];
+    __shared__ double rows[2][R][4];
+    __shared__ double next;
+    const int tid = threadIdx.x, b = blockIdx.x, G = gridDim.x;
+    const int col0 = (k & ~63) + tid;
+    const double* vp = V + static_cast<size_t>(k > 0 ? k - 1 : 0) * n;
+    const bool upd = k > 0;
+    int i = b;
+    if (i < k + 1) i += (k + 1 - i + G - 1) / G * G;
+
+    double a[R][CPT];
+    auto load_rows = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int iu = i0 + u * G;
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) {
+                const int j = col0 + 256 * c;
+                a[u][c] = (iu < n && j > k && j < n) ? C[static_cast<size_t>(iu) * n + j] : 0.0;
             }
         }
-        rot[i] = make_double2(c, s);
+    };
+
+    double v[CPT], w[CPT], x[CPT];
+    double s = 0.0;
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const int j = col0 + 256 * c;
+        const bool in = j >= k && j < n;
+        v[c] = in && upd ? vp[j] : 0.0;
+        w[c] = in && upd ? p_in[j] : 0.0;
+        x[c] = in ? C[static_cast<size_t>(k) * n + j] : 0.0;
     }
-    const unsigned long long b = __ballot(did);
-    if ((threadIdx.x & 63) == 0 && b) atomicAdd(count, __popcll(b));
+    const double tp = upd ? tau[k - 1] : 0.0;
+    const double pk = upd ? p_in[k] : 0.0;
+    load_rows(i);
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) s = fma(v[c], w[c], s);
+    s = block_sum_f64(s, red[0]);
+    const double h = 0.5 * tp * tp * s;
+    const double wk = fma(tp, pk, -h);           // v_k = 1
+    double q = 0.0;
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const int j = col0 + 256 * c;
+        w[c] = fma(tp, w[c], -h * v[c]);
+        x[c] = fma(-wk, v[c], x[c] - w[c]);
+        if (j == k && b == 0) d[k] = x[c];
+        if (j == k + 1) next = x[c];
+        if (j > k + 1) q = fma(x[c], x[c], q);   // zero past n
+    }
+    if (k + 1 >= n) return;                      // the last diagonal entry
+    q = block_sum_f64(q, red[1]);
+    const double x0 = next;
+    double t = 0.0, beta = x0, inv = 0.0;
+    if (q != 0.0) {
+        const double norm = sqrt(fma(x0, x0, q));
+        beta = x0 >= 0.0 ? -norm : norm;
+        t = (beta - x0) / beta;
+        inv = 1.0 / (x0 - beta);
+    }
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const int j = col0 + 256 * c;
+        x[c] = j == k + 1 ? 1.0 : (j > k + 1 ? x[c] * inv : 0.0);
+        if (b == 0 && j > k && j < n) V[static_cast<size_t>(k) * n + j] = x[c];
+    }
+    if (b == 0 && tid == 0) { tau[k] = t; e[k] = beta; }
+
+    for (int par = 0; i < n; i += R * G, par ^= 1) {
+        double acc[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int iu = i + u * G < n ? i + u * G : n - 1;
+            const double vi = upd ? vp[iu] : 0.0;
+            const double wi = upd ? fma(tp, p_in[iu], -h * vi) : 0.0;
+            acc[u] = 0.0;
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) {
+                const int j = col0 + 256 * c;
+                const double val = fma(-vi, w[c], fma(-wi, v[c], a[u][c]));
+                if (i + u * G < n && j > k && j < n) {
+                    if (tp != 0.0) C[static_cast<size_t>(iu) * n + j] = val;
+                    acc[u] = fma(val, x[c], acc[u]);
+                }
+            }
+        }
+        if (i + R * G < n) load_rows(i + R * G);
+#pragma unroll
+        for (int u = 0; u < R; ++u) acc[u] = wave_sum_f64(acc[u]);
+        if ((tid & 63) == 0) {
+#pragma unroll
+            for (int u = 0; u < R; ++u) rows[par][u][tid >> 6] = acc[u];
+        }
+        __syncthreads();
+        if (tid < R && i + tid * G < n) {
+            const double* r = rows[par][tid];
+            p_out[i + tid * G] = (r[0] + r[1]) + (r[2] + r[3]);
+        }
+    }
 }
 
-// Apply the round's rotations.  Rows blockIdx.y < N/2: the C blocks of row
-// pair a = blockIdx.y with column pairs b = thread index,
-// C_ab <- J_a^T C_ab J_b.  Rows beyond: row i of X, columns of pair b,
-// X_b <- X_b J_b.  Blocks whose two rotations are the identity are left alone.
-__global__ __launch_bounds__(256) void jacobi_apply_kernel(double* __restrict__ C, double* __restrict__ Xm, int n,
-                                                           int N, int r, const double2* __restrict__ rot) {
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    const int half = N / 2;
-    if (b >= half) return;
-    int pb, qb;
-    round_pair(N, r, b, pb, qb);
-    const double2 jb = rot[b];
-    const bool vpb = pb < n, vqb = qb < n;
-    if (static_cast<int>(blockIdx.y) < half) {
-        const int a = blockIdx.y;
-        const double2 ja = rot[a];
-        if (ja.y == 0.0 && jb.y == 0.0) return;
-        int pa, qa;
-        round_pair(N, r, a, pa, qa);
-        const bool vpa = pa < n, vqa = qa < n;
-        const size_t rp = static_cast<size_t>(pa) * n, rq = static_cast<size_t>(qa) * n;
-        const double x00 = (vpa && vpb) ? C[rp + pb] : 0.0;
-        const double x01 = (vpa && vqb) ? C[rp + qb] : 0.0;
-        const double x10 = (vqa && vpb) ? C[rq + pb] : 0.0;
-        const double x11 = (vqa && vqb) ? C[rq + qb] : 0.0;
-        // (C J_b): columns p, q
-        const double y00 = jb.x * x00 - jb.y * x01, y01 = jb.y * x00 + jb.x * x01;
-        const double y10 = jb.x * x10 - jb.y * x11, y11 = jb.y * x10 + jb.x * x11;
-        // J_a^T (C J_b): rows p, q
-        double z00 = ja.x * y00 - ja.y * y10, z01 = ja.x * y01 - ja.y * y11;
-        double z10 = ja.y * y00 + ja.x * y10, z11 = ja.y * y01 + ja.x * y11;
-        if (a == b && ja.y != 0.0) { z01 = 0.0; z10 = 0.0; }   // the entry the rotation annihilates
-        if (vpa && vpb) C[rp + pb] = z00;
-        if (vpa && vqb) C[rp + qb] = z01;
-        if (vqa && vpb) C[rq + pb] = z10;
-        if (vqa && vqb) C[rq + qb] = z11;
-    } else {
-        if (jb.y == 0.0) return;
-        const size_t row = static_cast<size_t>(blockIdx.y - half) * n;
-        const double x0 = vpb ? Xm[row + pb] : 0.0;
-        const double x1 = vqb ? Xm[row + qb] : 0.0;
-        if (vpb) Xm[row + pb] = jb.x * x0 - jb.y * x1;
-        if (vqb) Xm[row + qb] = jb.y * x0 + jb.x * x1;
+// (d_i, e_i-1^2) pairs for the Sturm counts; bounds = {lower and upper end of
+// the Gershgorin discs, |T|, smallest pivot}.  One workgroup.
+__global__ __launch_bounds__(256) void tridiagonal_prep_kernel(const double* __restrict__ d,
+                                                               const double* __restrict__ e, int n,
+                                                               double2* __restrict__ de, double* __restrict__ bounds) {
+    __shared__ double lo[256], hi[256], em[256];
+    double l = 1e308, h = -1e308, m = 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const double el = i > 0 ? e[i - 1] : 0.0, er = i + 1 < n ? e[i] : 0.0;
+        const double di = d[i], rad = fabs(el) + fabs(er);
+        de[i] = make_double2(di, el * el);
+        l = fmin(l, di - rad);
+        h = fmax(h, di + rad);
+        m = fmax(m, el * el);
+    }
+    lo[threadIdx.x] = l; hi[threadIdx.x] = h; em[threadIdx.x] = m;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (threadIdx.x < s) {
+            lo[threadIdx.x] = fmin(lo[threadIdx.x], lo[threadIdx.x + s]);
+            hi[threadIdx.x] = fmax(hi[threadIdx.x], hi[threadIdx.x + s]);
+            em[threadIdx.x] = fmax(em[threadIdx.x], em[threadIdx.x + s]);
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const double norm = fmax(fabs(lo[0]), fabs(hi[0]));
+        const double pad = 4e-16 * norm * sqrt(static_cast<double>(n));
+        bounds[0] = lo[0] - pad;
+        bounds[1] = hi[0] + pad;
+        bounds[2] = norm;
+        bounds[3] = 2.3e-308 * fmax(1.0, em[0]);
     }
 }
 
-// Descending order of the eigenvalues (ties by index); sigma = sqrt(max(0,
-// lambda)) in that order.
-__global__ __launch_bounds__(256) void eig_sort_kernel(const double* __restrict__ C, int n, double* __restrict__ lam,
-                                                       int* __restrict__ order, float* __restrict__ sigma) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const double li = C[static_cast<size_t>(i) * n + i];
-    int rank = 0;
-    for (int j = 0; j < n; ++j) {
-        const double lj = C[static_cast<size_t>(j) * n + j];
-        rank += (lj > li) || (lj == li && j < i);
+// Eigenvalue j (descending), one wave each: the number of eigenvalues below x
+// is the number of negative pivots of T - x; each round every lane counts at
+// one of 64 points of the interval.
+__global__ __launch_bounds__(256) void bisect_kernel(const double2* __restrict__ de, int n,
+                                                     const double* __restrict__ bounds, double* __restrict__ lam,
+                                                     float* __restrict__ sigma) {
+    const int j = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (j >= n) return;
+    const int lane = threadIdx.x & 63, below = n - 1 - j;
+    double lo = bounds[0], hi = bounds[1];
+    const double pivmin = bounds[3];
+    for (int round = 0; round < kSections; ++round) {
+        const double width = (hi - lo) * (1.0 / 65.0);
+        const double x = fma(width, lane + 1.0, lo);
+        int count = 0;
+        double q = 1.0;
+#pragma unroll 8
+        for (int i = 0; i < n; ++i) {
+            const double2 t = de[i];
+            q = fma(-t.y, recip_f64(q), t.x - x);
+            if (fabs(q) < pivmin) q = -pivmin;
+            count += q < 0.0;
+        }
+        const unsigned long long above = __ballot(count > below);
+        const int first = above ? __builtin_ctzll(above) : 64;
+        const double base = lo;
+        if (first < 64) hi = fma(width, first + 1.0, base);
+        if (first > 0) lo = fma(width, static_cast<double>(first), base);
     }
-    order[rank] = i;
-    lam[rank] = li;
-    if (sigma) sigma[rank] = static_cast<float>(sqrt(li > 0.0 ? li : 0.0));
+    if (lane == 0) {
+        const double l = bounds[2] == 0.0 ? 0.0 : 0.5 * (lo + hi);
+        lam[j] = l;
+        if (sigma) sigma[j] = static_cast<float>(sqrt(l > 0.0 ? l : 0.0));
+    }
 }
 
-// Xr[j][i] = X[i][order[j]] for the leading r_max eigenvectors.
-__global__ __launch_bounds__(256) void gather_kernel(const double* __restrict__ Xm, int n, const int* __restrict__ order,
-                                                     int r_max, double* __restrict__ Xr) {
-    const size_t idx = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (idx >= static_cast<size_t>(r_max) * n) return;
-    const int j = static_cast<int>(idx / n), i = static_cast<int>(idx % n);
-    Xr[idx] = Xm[static_cast<size_t>(i) * n + order[j]];
+// One inverse iteration of vectors j0 .. j0 + nb - 1, a lane each: Gaussian
+// elimination of T - lambda_j with partial pivoting, the right-hand side
+// (the last iterate, |T| scaled; a fixed pseudo-random vector at first)
+// carried along, then back substitution.  S: the rows of the upper factor
+// (reciprocal pivot, two off-diagonals) and the reduced right-hand side, nb
+// of each per row; Z[i][j] the iterates, scale[j] their reciprocal norms.
+__global__ __launch_bounds__(64) void inverse_iteration_kernel(const double* __restrict__ d,
+                                                               const double* __restrict__ e, int n,
+                                                               const double* __restrict__ bounds,
+                                                               const double* __restrict__ lam, int j0, int nb,
+                                                               int r_max, bool first, double* __restrict__ S,
+                                                               double* __restrict__ Z, double* __restrict__ scale) {
+    const int t = blockIdx.x * 64 + threadIdx.x;
+    if (t >= nb) return;
+    const int j = j0 + t;
+    const size_t plane = static_cast<size_t>(n) * nb;
+    double *U0 = S + t, *U1 = U0 + plane, *U2 = U1 + plane, *Y = U2 + plane;
+    const double norm = bounds[2] > 0.0 ? bounds[2] : 1.0, tiny = 1.1e-16 * norm, l = lam[j];
+    const double sc = first ? norm : norm * scale[j];
+    auto rhs = [&](int i) -> double {
+        if (!first) return sc * Z[static_cast<size_t>(i) * r_max + j];
+        uint32_t h = static_cast<uint32_t>(i) * 0x9E3779B1u ^ static_cast<uint32_t>(j + 1) * 0x85EBCA77u;
+        h ^= h >> 15; h *= 0x2C1B3C6Du; h ^= h >> 12; h *= 0x297A2D39u; h ^= h >> 15;
+        return sc * (static_cast<double>(h) * 0x1p-31 - 1.0);
+    };
+    double a = d[0] - l, b = n > 1 ? e[0] : 0.0, y = rhs(0);
+#pragma unroll 4
+    for (int i = 0; i + 1 < n; ++i) {
+        const double ei = e[i], dn = d[i + 1] - l, en = i + 2 < n ? e[i + 1] : 0.0, yn = rhs(i + 1);
+        const size_t at = static_cast<size_t>(i) * nb;
+        const bool keep = fabs(a) >= fabs(ei);
+        double pivot = keep ? a : ei;
+        if (pivot == 0.0) pivot = tiny;
+        const double ui = recip_f64(pivot), m = (keep ? ei : a) * ui;
+        U0[at] = ui;
+        U1[at] = keep ? b : dn;
+        U2[at] = keep ? 0.0 : en;
+        Y[at] = keep ? y : yn;
+        const double a2 = keep ? fma(-m, b, dn) : fma(-m, dn, b);
+        b = keep ? en : -m * en;
+        y = keep ? fma(-m, y, yn) : fma(-m, yn, y);
+        a = a2;
+    }
+    if (fabs(a) < tiny) a = tiny;
+    double x1 = y * recip_f64(a), x2 = 0.0, ss = x1 * x1;
+    Z[static_cast<size_t>(n - 1) * r_max + j] = x1;
+#pragma unroll 4
+    for (int i = n - 2; i >= 0; --i) {
+        const size_t at = static_cast<size_t>(i) * nb;
+        const double x = fma(-U2[at], x2, fma(-U1[at], x1, Y[at])) * U0[at];
+        Z[static_cast<size_t>(i) * r_max + j] = x;
+        ss = fma(x, x, ss);
+        x2 = x1;
+        x1 = x;
+    }
+    scale[j] = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
+}
+
+// Modified Gram-Schmidt within each run of eigenvalues closer than kCluster
+// |T|, one workgroup per run (the others leave at once).  Vectors of
+// eigenvalue zero are multiplied by sigma = 0 afterwards and stay as they are.
+__global__ __launch_bounds__(256) void orthogonalise_kernel(const double* __restrict__ lam,
+                                                            const double* __restrict__ bounds, int n, int r_max,
+                                                            double* __restrict__ Z, double* __restrict__ scale) {
+    __shared__ double red[2][4];
+    const int head = blockIdx.x;
+    const double tol = kCluster * bounds[2];
+    auto close = [&](int m) { return m > 0 && m < r_max && lam[m] > 0.0 && lam[m - 1] - lam[m] <= tol; };
+    if (close(head)) return;
+    int par = 0;
+    for (int m = head + 1; close(m); ++m) {
+        double sm = scale[m];
+        double ss = 0.0;
+        for (int q = head; q < m; ++q) {
+            const double sq = scale[q];
+            double dot = 0.0;
+            for (int i = threadIdx.x; i < n; i += 256) {
+                const size_t at = static_cast<size_t>(i) * r_max;
+                dot = fma(Z[at + m] * sm, Z[at + q] * sq, dot);
+            }
+            dot = block_sum_f64(dot, red[par]);
+            par ^= 1;
+            ss = 0.0;
+            for (int i = threadIdx.x; i < n; i += 256) {
+                const size_t at = static_cast<size_t>(i) * r_max;
+                const double z = fma(-dot, Z[at + q] * sq, Z[at + m] * sm);
+                Z[at + m] = z;
+                ss = fma(z, z, ss);
+            }
+            sm = 1.0;
+        }
+        ss = block_sum_f64(ss, red[par]);
+        par ^= 1;
+        if (threadIdx.x == 0) scale[m] = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
+        __syncthreads();
+    }
+}
+
+// X = Q Z: the reflectors applied in reverse to vector j, one workgroup each,
+// CPT entries per thread in registers; the next reflector is loaded while
+// this one's dot product is summed.  Xr[j][i] = X[i][j].
+template <int CPT>
+__global__ __launch_bounds__(256) void back_transform_kernel(const double* __restrict__ V,
+                                                             const double* __restrict__ tau, int n, int r_max,
+                                                             const double* __restrict__ Z,
+                                                             const double* __restrict__ scale,
+                                                             double* __restrict__ Xr) {
+    __shared__ double red[2][4];
+    const int j = blockIdx.x, tid = threadIdx.x;
+    double z[CPT], v[CPT];
+    const double sc = scale[j];
+    auto load = [&](int k) {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            const int i = tid + 256 * c;
+            v[c] = i > k && i < n ? V[static_cast<size_t>(k) * n + i] : 0.0;
+        }
+    };
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const int i = tid + 256 * c;
+        z[c] = i < n ? sc * Z[static_cast<size_t>(i) * r_max + j] : 0.0;
+    }
+    if (n > 2) load(n - 3);
+    for (int k = n - 3; k >= 0; --k) {
+        double dot = 0.0, u[CPT];
+        const double t = tau[k];
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            u[c] = v[c];
+            dot = fma(v[c], z[c], dot);
+        }
+        if (k > 0) load(k - 1);
+        dot = -t * block_sum_f64(dot, red[k & 1]);
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) z[c] = fma(dot, u[c], z[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const int i = tid + 256 * c;
+        if (i < n) Xr[static_cast<size_t>(j) * n + i] = z[c];
+    }
 }
 
 // sign[j] = +-1 so that the largest-magnitude entry (first index on ties) of
@@ -370,58 +601,73 @@ size_t comp_workspace_bytes(int d_out, int d_in, int r_max) {
     return comp_layout(d_out, d_in, r_max).total;
 }
 
+namespace {
+
+// Columns per thread for `cols` columns over 256 threads.
+template <typename F>
+void by_columns(int cols, F f) {
+    if (cols <= 256) f(std::integral_constant<int, 1>());
+    else if (cols <= 512) f(std::integral_constant<int, 2>());
+    else if (cols <= 1024) f(std::integral_constant<int, 4>());
+    else if (cols <= 2048) f(std::integral_constant<int, 8>());
+    else if (cols <= 4096) f(std::integral_constant<int, 16>());
+    else f(std::integral_constant<int, 32>());
+}
+
+}  // namespace
+
 hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uint16_t* A, uint16_t* B, float* sigma,
                                      void* ws, hipStream_t st, int* sweeps_out) {
     const int d_out = w.d_out, d_in = w.d_in;
     const bool right = d_in <= d_out;              // Gram over d_in: eigenvectors are V
     const int n = right ? d_in : d_out;
-    const int N = n + (n & 1);
     const CompLayout l = comp_layout(d_out, d_in, r_max);
-    char* b = static_cast<char*>(ws);
-    double* E = reinterpret_cast<double*>(b + l.E);
-    double* C = reinterpret_cast<double*>(b + l.C);
-    double* Xm = reinterpret_cast<double*>(b + l.X);
-    double2* rot = reinterpret_cast<double2*>(b + l.rot);
-    double* lam = reinterpret_cast<double*>(b + l.lam);
-    int* order = reinterpret_cast<int*>(b + l.order);
-    int* count = reinterpret_cast<int*>(b + l.count);
-    double* delta = reinterpret_cast<double*>(b + l.delta);
-    double* sign = reinterpret_cast<double*>(b + l.sign);
-    double* Xr = reinterpret_cast<double*>(b + l.Xr);
-    double* P = reinterpret_cast<double*>(b + l.P);
-    hipError_t e;
+    char* base = static_cast<char*>(ws);
+    auto at = [&](size_t off) { return reinterpret_cast<double*>(base + off); };
+    double *E = at(l.E), *C = at(l.C), *V = at(l.V), *tau = at(l.tau), *lam = at(l.lam), *d = at(l.d), *e = at(l.e);
+    double *p[2] = {at(l.p), at(l.p) + n}, *bounds = at(l.bounds), *scale = at(l.scale), *sign = at(l.sign);
+    double *Xr = at(l.Xr), *P = at(l.P);
+    double2* de = reinterpret_cast<double2*>(base + l.de);
+    hipError_t err;
 
     const size_t total = static_cast<size_t>(d_out) * d_in;
     hipLaunchKernelGGL(residual_kernel, dim3(grid1(total)), dim3(256), 0, st, W, w, E);
     // Gram: C[i][j] = sum_k E_k,i E_k,j over the larger side
     if (right) gemm<false, false>(E, 1, d_in, E, 1, d_in, n, n, d_out, C, n, st);
     else gemm<true, true>(E, d_in, 1, E, d_in, 1, n, n, d_in, C, n, st);
-    hipLaunchKernelGGL(jacobi_init_kernel, dim3(grid1(static_cast<size_t>(n) * n)), dim3(256), 0, st, C, Xm, n, count,
-                       delta);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
 
-    int sweeps = 0;
-    for (; sweeps < kMaxSweeps; ++sweeps) {
-        for (int r = 0; r < N - 1; ++r) {
-            hipLaunchKernelGGL(jacobi_rot_kernel, dim3(grid1(N / 2)), dim3(256), 0, st, C, n, N, r, delta, rot,
-                               count + sweeps);
-            hipLaunchKernelGGL(jacobi_apply_kernel, dim3(grid1(N / 2), N / 2 + n), dim3(256), 0, st, C, Xm, n, N, r,
-                               rot);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        int rotations = 0;
-        if ((e = hipMemcpyAsync(&rotations, count + sweeps, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess)
-            return e;
-        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-        if (rotations == 0) break;
+    for (int k = 0; k < n; ++k) {
+        by_columns(n - (k & ~63), [&](auto cpt) {
+            constexpr int CPT = decltype(cpt)::value, R = CPT > 8 ? 2 : 4;
+            hipLaunchKernelGGL((householder_step_kernel<CPT, R>), dim3(n < 256 ? n : 256), dim3(256), 0, st, C, n, k, V,
+                               p[k & 1], p[(k & 1) ^ 1], tau, d, e);
+        });
     }
-    if (sweeps_out) *sweeps_out = sweeps;
-    if (sweeps == kMaxSweeps) return hipErrorNotReady;       // did not converge (reported by the caller)
-
-    hipLaunchKernelGGL(eig_sort_kernel, dim3(grid1(n)), dim3(256), 0, st, C, n, lam, order, sigma);
+    hipLaunchKernelGGL(tridiagonal_prep_kernel, dim3(1), dim3(256), 0, st, d, e, n, de, bounds);
+    hipLaunchKernelGGL(bisect_kernel, dim3((n + 3) / 4), dim3(256), 0, st, de, n, bounds, lam, sigma);
     if (r_max > 0) {
-        hipLaunchKernelGGL(gather_kernel, dim3(grid1(static_cast<size_t>(r_max) * n)), dim3(256), 0, st, Xm, n,
-                           order, r_max, Xr);
+        // C is free now: the eliminations of n / 4 vectors at a time (4 planes
+        // of n each), the iterates in P until the product with E needs it
+        const int batch = n < 4 ? 1 : n / 4;
+        for (int sweep = 0; sweep < kInverseSweeps; ++sweep) {
+            for (int j0 = 0; j0 < r_max; j0 += batch) {
+                const int nb = r_max - j0 < batch ? r_max - j0 : batch;
+                hipLaunchKernelGGL(inverse_iteration_kernel, dim3((nb + 63) / 64), dim3(64), 0, st, d, e, n, bounds,
+                                   lam, j0, nb, r_max, sweep == 0, C, P, scale);
+            }
+            hipLaunchKernelGGL(orthogonalise_kernel, dim3(r_max), dim3(256), 0, st, lam, bounds, n, r_max, P, scale);
+        }
+        by_columns(n, [&](auto cpt) {
+            hipLaunchKernelGGL((back_transform_kernel<decltype(cpt)::value>), dim3(r_max), dim3(256), 0, st, V, tau, n,
+                               r_max, P, scale, Xr);
+        });
+    }
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    // W has been read, and a fault of the work so far is reported by this call
+    if ((err = hipStreamSynchronize(st)) != hipSuccess) return err;
+    if (sweeps_out) *sweeps_out = r_max > 0 ? kInverseSweeps : 1;
+
+    if (r_max > 0) {
         if (right) {
             // P[o][j] = sum_c E[o][c] V[c][j]
             gemm<true, true>(E, d_in, 1, Xr, d_in, 1, d_out, r_max, d_in, P, r_max, st);

@@ -215,3 +215,76 @@ def test_full_size_4096_rank_128_against_lapack(capsys):
     with capsys.disabled():
         print("\n[cl_build_compensation 4096 x 4096, r_max 128: %.2f s, %d Jacobi sweeps, residual/tail %.8f]"
               % (dt, sweeps, ratio))
+
+
+def _known_spectrum(n, big, spectra, seed):
+    """A matrix [n][big] with the given singular values: random orthogonal
+    blocks of the sizes of ``spectra``, rows and columns shuffled."""
+    g = np.random.default_rng(seed)
+    W = np.zeros((n, big))
+    at = 0
+    for s in spectra:
+        m = len(s)
+        U, V = (np.linalg.qr(g.standard_normal((m, m)))[0] for _ in range(2))
+        W[at:at + m, at:at + m] = (U * s) @ V.T
+        at += m
+    return np.ascontiguousarray(W[g.permutation(n)][:, g.permutation(big)], dtype=np.float32)
+
+
+def _build(E, r_max):
+    """Factors of the residual E itself: a backbone of zeros is subtracted."""
+    d_out, d_in = E.shape
+    z = torch.zeros((d_out, d_in // 128), dtype=torch.float16, device="cuda")
+    w = cl.QWeight(torch.zeros((d_out, d_in // 8), dtype=torch.int32, device="cuda"), z, z.clone(), d_out, d_in, 4, 128)
+    A, B, sigma = cl.build_compensation(torch.from_numpy(E).cuda(), w, r_max)
+    return _host16(A), _host16(B), sigma.cpu().numpy().astype(np.float64)
+
+
+def _check_known(E, s_ref, A, B, sigma, r_max):
+    """Against the known singular values: E is fp32, which moves them by at
+    most |E - W|_F <= 2^-24 |E|_F (Weyl); the Gram matrix in fp64 resolves
+    sqrt(n 2^-52) of the largest.  The factors' rows and columns carry one fp16
+    rounding, so their inner products are those of the exact ones to 2^-10 of
+    the norms and the residual of rank r is the tail to 2^-9 of the energy."""
+    norm = np.sqrt(np.sum(s_ref ** 2))
+    assert np.max(np.abs(sigma - s_ref)) <= 2.0 ** -23 * norm + np.sqrt(len(s_ref) * 2.0 ** -52) * s_ref[0]
+    lead = s_ref[:r_max]
+    bound = 2.0 ** -10 * np.sqrt(np.outer(lead, lead)) + 1e-6 * s_ref[0]
+    assert np.all(np.abs(B.T @ B - np.diag(lead)) <= bound)
+    assert np.all(np.abs(A @ A.T - np.diag(lead)) <= bound)
+    tail = float(np.sum(s_ref[r_max:] ** 2))
+    R = E.astype(np.float64) - B @ A
+    assert abs(float(np.sum(R * R)) - tail) <= 2.0 ** -9 * norm ** 2
+
+
+@pytest.mark.parametrize("n,r_max", [(1, 1), (2, 2), (3, 2), (5, 3), (64, 16), (65, 65), (255, 7), (257, 130),
+                                     (513, 20), (1025, 65), (2050, 16), (4100, 9)])
+def test_every_width_of_the_tridiagonal_solver(n, r_max):
+    """One size for each number of columns a thread owns and for each edge of
+    it; fewer rows than workgroups; vectors in one batch and in several."""
+    g = np.random.default_rng(n)
+    spectra, left = [], n
+    while left:
+        m = min(left, 50)
+        spectra.append(np.sort(g.uniform(0.1, 2.0, m))[::-1])
+        left -= m
+    E = _known_spectrum(n, -(-n // 128) * 128, spectra, n)
+    s_ref = np.sort(np.concatenate(spectra))[::-1]
+    A, B, sigma = _build(E, r_max)
+    _check_known(E, s_ref, A, B, sigma, r_max)
+
+
+@pytest.mark.parametrize("spectra,r_max", [
+    ([[1.0] * 40, [1.0] * 24], 64),                        # one value, decoupled blocks
+    ([[2.0] * 5 + [1.0] * 30 + [0.5] * 29], 50),           # clusters cut by r_max
+    ([[3.0, 1.0], [3.0, 1.0, 0.0], [0.0] * 59], 20),       # rank 4, vectors past the rank
+    ([[1.0 - 1e-9 * i for i in range(64)]], 64),           # closer than the orthogonalisation's bound
+    ([[1e-9 * 2.0 ** -i for i in range(20)], [0.0] * 44], 8),
+])
+def test_repeated_and_zero_singular_values(spectra, r_max):
+    s_ref = np.sort(np.concatenate([np.asarray(s) for s in spectra]))[::-1]
+    scale = max(1.0, 1.0 / s_ref[0])                       # fp16 holds the factors of sigma near 1
+    s_ref = s_ref * scale
+    E = _known_spectrum(64, 128, [np.asarray(s) * scale for s in spectra], 7)
+    A, B, sigma = _build(E, r_max)
+    _check_known(E, s_ref, A, B, sigma, r_max)
