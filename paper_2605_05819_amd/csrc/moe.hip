@@ -33,8 +33,11 @@
 //    arithmetic as the dense decode kernel: mask-only unpack into subnormal
 //    fp16 lanes, v_dot2, per-chunk scale and zero in fp32, B t in the same
 //    partial sums, transposing butterfly, fixed-order K-slice reduction.
-//  * moe_mfma_kernel: with several slots per expert (4-bit codes), the
-//    expert's rows against its slots on MFMA (slots as the columns).
+//  * moe_stream_kernel: 4-bit codes of many experts, the tiles of all of them
+//    shared evenly by the resident workgroups and streamed through MFMA.
+//  * moe_mfma_kernel: with several slots per expert (4-bit codes) where the
+//    streamed kernel does not apply, the expert's rows against its slots on
+//    MFMA (slots as the columns).
 
 #include "cl_device.h"
 #include "cl_internal.h"
@@ -56,7 +59,7 @@ namespace {
 constexpr int rows_per_wave(int bits) { return bits == 4 ? 4 : 2; }
 constexpr int kMaxSlots = 1024;      // T * k
 constexpr int kMaxExperts = 1024;
-constexpr int kTab = 8;              // ints per active-expert table entry
+constexpr int kTab = 24;             // ints per active-expert table entry
 constexpr int kMaxMoeWin = 4;        // linears per window
 // Direct path (moe_direct_kernel): at most this many slots; row batches per
 // wave counted for 4 waves of 4 rows per row set of LG lanes (64 rows per
@@ -73,6 +76,12 @@ constexpr int direct_batches(int lg, int cpl) { return cpl == 2 ? 2 : (lg == 64 
 // pipeline's tail stopped re-reading code blocks: 4 x 1 143.7 us, 8 x 1
 // 150.5, 2 x 1 153.0, 6 x 1 161.7, 4 x 2 ~160 (165 VGPRs at 4 x 1: three
 // waves per SIMD against two).
+// Streamed path: workgroups of 4 waves that share the tiles (two per CU), and
+// the tiles in flight per wave.
+constexpr int kStreamBlocks = 512;
+constexpr int kStreamDepth = 2;
+constexpr int kStreamMaxRows = (1 << 29) / kMaxSlots - 1;   // 31-bit byte offsets of fp32 outputs
+constexpr int kStreamMinExperts = 32, kStreamMinWidth = 36 << 10;
 constexpr int kMoeTpw = 4;
 constexpr int kMoeNbuf = 1;
 
@@ -108,7 +117,7 @@ struct MoeArgs {
     // workspace
     int* n_active;
     int* table;              // [max_active][kTab]: expert, first sorted index, slot count, first slot,
-                             // then each linear's rank
+                             // then each linear's rank, then its first 16 slots (padded with the first)
     int* sorted;             // [T*k] slot ids grouped by expert, slot order within
     f16x2* xp;               // [rows][d_in/2]
     float* sx;               // [rows][chunks]
@@ -256,6 +265,12 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
                 if (li == 0 && quad == 0) {
                     a.sorted[cnt_lt + pos] = sl;
                     if (pos == 0) a.table[kTab * j + 3] = sl;
+                }
+                if (li == 0 && quad == 0) {
+                    // entries 8 + pos, and past the last slot the first again
+                    if (pos < 16) a.table[kTab * j + 8 + pos] = sl;
+                    if (pos == 0)
+                        for (int u = ne; u < 16; ++u) a.table[kTab * j + 8 + u] = sl;
                 }
                 mys[pos] = sl;
                 if (dyn) {
@@ -875,6 +890,372 @@ __global__ __launch_bounds__(64 * NWV) void moe_direct_kernel(MoeArgs a) {
     }
 }
 
+// One value to element idx of an array of n; idx < 0: dropped by the bounds
+// check.  n * 4 bytes must stay below 2^31.
+__device__ __forceinline__ void buffer_store_out(void* y, uint32_t n, int idx, float v, int out) {
+    const uint32_t es = out == DT_FP32 ? 4 : 2;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(y, 0, n * es, 0x00027000);
+    const uint32_t off = static_cast<uint32_t>(idx) * es;
+    if (out == DT_FP32)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rsrc, idx < 0 ? 0xFFFFFFF0u : off, 0, 0);
+    else
+        __builtin_amdgcn_raw_buffer_store_b16(out == DT_FP16 ? f32_to_f16_bits(v) : f32_to_bf16_bits(v), rsrc,
+                                              idx < 0 ? 0xFFFFFFF0u : off, 0, 0);
+}
+
+// The 4-bit backbone off the one-launch path, rows of at most 4096 codes: the
+// expert's rows against its slots on v_mfma_f32_16x16x32_f16, streamed.
+// Bound by HBM (the routed experts' codes).  The tiles of 16 rows of every
+// routed expert and linear form one list (expert, linear, tile) that the
+// resident workgroups share evenly: a workgroup's start (table entries, slot
+// ids, activations: three dependent round trips) is paid once or twice per
+// call instead of once per 64 rows, and no last wave of workgroups is nearly
+// empty.  A workgroup's waves split K into KW = a.ks parts of NBK 128-code
+// blocks and the tiles into blockDim / 64 / KW sets; D tiles per wave are in
+// flight ahead of the one computed, across the borders of experts.  A pass of
+// 16 slots keeps its activations (MFMA A operand, NBK x 64 bytes per lane) and
+// its t operand in registers, so a tile costs its codes, scales, zeros (lane
+// group g loads those of every fourth part; a shuffle hands them on) and
+// factor row only.  Absent slots of a pass repeat a present one; their rows of
+// the product are not stored.  Codes become the exact integers q - z, each
+// quantization group's partial is scaled in fp32, the rank term is MFMA steps
+// over [t | B_e] with t as fp16 hi and lo parts of t 2^-e (e the exponent of
+// the step's largest |t| of the slot, restored in fp32: neither overflow nor
+// fp16's subnormal range is met); the K parts meet in LDS in a fixed order;
+// one rounding.  Two tiles in flight (four layers of 128 experts, 2048 x 768, at
+// 512 slots: 502 us; three 510, one 527) and two workgroups per CU (one: 1.6
+// times the time; 233 registers do not fit three).
+// Where the line lies: NBK <= 4 blocks on KW <= 8 waves keep the activations
+// within 64 registers; groups of 32 codes (four scales per block) were 2 %
+// slower than on the kernels below, and so were few experts or short rows,
+// where a workgroup's start is not spread over enough tiles (two layers as
+// above with at most 16 experts reached: 84 against 78 us; 64 experts of 512 x
+// 256: 85 against 75).  The rule reads only what the linears of a window
+// share, so a window's outputs equal the single calls'.  gate,up / down of
+// the layer above, traced: 65 / 50 -> 59 / 39 us at 512 slots, 36 / 23 -> 31 /
+// 21 us at 64 (against moe_mfma_kernel and moe_kernel).
+template <int NBK, int GPB, int KW, int D>
+__global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves_per_eu(2))) void moe_stream_kernel(MoeArgs a) {
+    extern __shared__ float red[];                // [2][waves][4][64]
+    constexpr int SPG = 4 / GPB, NP = NBK * GPB, NU = (NP + 3) / 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int waves = KW > 4 ? KW : 4, RW = waves / KW;
+    const int kw = wave % KW, rw = wave / KW;
+    const int g = lane >> 4, r = lane & 15;
+    // this workgroup's share [beg, end) of the list
+    const int per = a.lin[a.n - 1].blk_end;       // tiles per expert, all linears
+    const long long total = static_cast<long long>(*a.n_active) * per;
+    const int beg = static_cast<int>(total * blockIdx.x / gridDim.x);
+    const int end = static_cast<int>(total * (blockIdx.x + 1) / gridDim.x);
+    if (beg >= end) return;
+    const int ae0 = beg / per;
+    // lane i: the table entry of active expert ae0 + i (a share spans few)
+    const int elast = (end - 1) / per;
+    const int* ent = a.table + kTab * min(ae0 + lane, elast);
+    const int v_e = ent[0], v_sbeg = ent[1], v_scnt = ent[2];
+    int v_rank[kMaxMoeWin];
+#pragma unroll
+    for (int i = 0; i < kMaxMoeWin; ++i) v_rank[i] = ent[4 + i];
+    auto of = [&](int v, int ae) { return __builtin_amdgcn_readlane(v, ae - ae0); };
+    auto rank_of = [&](int ae, int li) {
+        return of(li == 0 ? v_rank[0] : li == 1 ? v_rank[1] : li == 2 ? v_rank[2] : v_rank[3], ae);
+    };
+
+    const int K = a.d_in;
+    const int nkb = (K + 127) / 128, kb0 = kw * NBK;
+    const int words_row = K / 8;
+    const int groups = K / a.G;
+    const uint32_t mlo = __builtin_amdgcn_readfirstlane(0x000F000Fu);
+    const uint32_t mhi = __builtin_amdgcn_readfirstlane(0x00F000F0u);
+    const uint32_t bias = 0x64006400u;
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const f32x4 fzero = {0.f, 0.f, 0.f, 0.f};
+    // this lane's word of each block, and the quantization group of its parts
+    // (part p = GPB b + q: codes 32 SPG q .. of block b)
+    int wo[NBK], go[NU];
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) wo[b] = min((kb0 + b) * 16 + 4 * g, words_row - 4);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int p = min(g + 4 * u, NP - 1);
+        go[u] = min(kb0 * 128 + 32 * SPG * p, K - 1) / a.G;
+    }
+    const int from = 4 * r;                       // shuffle source (bytes) of part p: from + 64 (p % 4)
+
+    // position in the list; the loads run D steps ahead of the arithmetic
+    struct Pos {
+        int ae, li, lo, hi, t, p0;
+    };
+    auto enter = [&](Pos& c) {                    // the share's tiles of (ae, li)
+        const int base = c.ae * per + (c.li ? a.lin[c.li - 1].blk_end : 0);
+        c.lo = max(beg - base, 0);
+        c.hi = min(end - base, a.lin[c.li].blk_end - (c.li ? a.lin[c.li - 1].blk_end : 0));
+        c.t = c.lo;
+        c.p0 = 0;
+    };
+    auto over = [&](const Pos& c) { return c.ae > elast; };
+    auto advance = [&](Pos& c) {                  // true: another (ae, li) or pass
+        c.t += RW;
+        if (c.t < c.hi) return false;
+        c.p0 += 16;
+        c.t = c.lo;
+        if (c.p0 < of(v_scnt, c.ae)) return true;
+        Pos nx = c;
+        do {
+            if (++nx.li == a.n) { nx.li = 0; ++nx.ae; }
+            if (over(nx)) {                       // tiles of the last segment stay addressable
+                c.ae = nx.ae;
+                return true;
+            }
+            enter(nx);
+        } while (nx.lo >= nx.hi);
+        c = nx;
+        return true;
+    };
+
+    struct Tile {
+        u32x4 w[NBK];
+        u32x4 b;
+        uint32_t s[NU], z[NU];
+    };
+    // what the loads need of the segment (ae, li)
+    const uint32_t* q_seg = nullptr;
+    const uint16_t *s_seg = nullptr, *z_seg = nullptr, *b_seg = nullptr;
+    int d_out_seg = 0, r_max_seg = 0, ko_seg = 0;
+    bool pre_seg = false;
+    auto rank_rows_aligned = [&](const MoeLin& L) {
+        return L.r_max > 0 && (L.r_max & 7) == 0 && (reinterpret_cast<uintptr_t>(L.B) & 15) == 0;
+    };
+    auto load_segment = [&](const Pos& c) {
+        const MoeLin& L = a.lin[c.li];
+        const size_t e = of(v_e, c.ae);
+        q_seg = L.q + e * L.q_stride;
+        s_seg = L.s + e * L.sz_stride;
+        z_seg = L.z + e * L.sz_stride;
+        b_seg = L.B + e * L.b_stride;
+        d_out_seg = L.d_out;
+        r_max_seg = L.r_max;
+        pre_seg = rank_rows_aligned(L) && 32 * kw < rank_of(c.ae, c.li);
+        ko_seg = 32 * kw + 8 * g + 8 <= L.r_max ? 32 * kw + 8 * g : 0;
+    };
+    auto load_tile = [&](const Pos& c, Tile& t) {
+        // a tile past the segment, or past the list, repeats one row of the last
+        const bool live = c.t + rw < c.hi && !over(c);
+        const int row0 = 16 * min(c.t + rw, c.hi - 1);
+        const int rr = live ? min(r, d_out_seg - 1 - row0) : 0;
+        const uint32_t* qt = q_seg + static_cast<size_t>(row0) * words_row;
+        const uint16_t* st = s_seg + static_cast<size_t>(row0) * groups;
+        const uint16_t* zt = z_seg + static_cast<size_t>(row0) * groups;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            t.s[u] = st[static_cast<uint32_t>(rr * groups + go[u])];
+            t.z[u] = zt[static_cast<uint32_t>(rr * groups + go[u])];
+        }
+        // without a prefetched factor row: a line of the codes
+        const char* bt = pre_seg ? reinterpret_cast<const char*>(b_seg + static_cast<size_t>(row0) * r_max_seg)
+                                 : reinterpret_cast<const char*>(qt);
+        t.b = *reinterpret_cast<const u32x4*>(bt + static_cast<uint32_t>(pre_seg ? 2 * (rr * r_max_seg + ko_seg) : 0));
+#pragma unroll
+        for (int b = 0; b < NBK; ++b)
+            t.w[b] = __builtin_nontemporal_load(
+                reinterpret_cast<const u32x4*>(qt + static_cast<uint32_t>(rr * words_row + wo[b])));
+    };
+
+    // the pass's slots and activations
+    int sl = 0, osl[4], osl_k = 0;
+    u32x4 x[NBK][4];
+    auto load_x = [&](const Pos& c) {
+        const int scnt = of(v_scnt, c.ae);
+        sl = c.p0 == 0 ? a.table[kTab * c.ae + 8 + r] : a.sorted[of(v_sbeg, c.ae) + (c.p0 + r < scnt ? c.p0 + r : 0)];
+        const int xrow = a.x_per_slot ? sl : sl / a.k;
+        const u32x4* xr = reinterpret_cast<const u32x4*>(a.xp + static_cast<size_t>(xrow) * (K / 2));
+#pragma unroll
+        for (int b = 0; b < NBK; ++b) {
+            const int kb = min(kb0 + b, nkb - 1);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                x[b][t] = xr[GPB == 1 ? wo[b] + t : (kb * 128 + 32 * t < K ? kb * 16 + 4 * t + g : g)];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) osl[q] = __shfl(sl, 4 * g + q, 64);
+        osl_k = __shfl(sl, 4 * g + (kw & 3), 64);
+    };
+    // t operand of the rank step at factor column kr, and the factors that
+    // restore it for this lane's accumulators (slots 4 g .. 4 g + 3)
+    struct TOp {
+        u32x4 hi, lo;
+        f32x4 up;
+    };
+    auto t_operand = [&](const MoeLin& L, int rank, int kr) {
+        int rs = rank;
+        if (L.slot_rank) {
+            const int v = L.slot_rank[sl];
+            rs = v < 0 ? 0 : (v > L.r_max ? L.r_max : v);
+        }
+        const float* trow = L.t + static_cast<size_t>(sl) * L.r_max;
+        const int k = kr + 8 * g;
+        float v[8], m = 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float tv = trow[k + q < L.r_max ? k + q : 0];
+            v[q] = k + q < rs ? tv : 0.f;
+            m = fmaxf(m, fabsf(v[q]));
+        }
+        m = fmaxf(m, __shfl_xor(m, 16, 64));
+        m = fmaxf(m, __shfl_xor(m, 32, 64));
+        const uint32_t ex = min(max(__builtin_bit_cast(uint32_t, m) >> 23, 1u), 253u);
+        const float down = __builtin_bit_cast(float, (254u - ex) << 23);
+        const float up = __builtin_bit_cast(float, ex << 23);
+        TOp o;
+        uint32_t h[4], l[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) split_f16x2(v[2 * q] * down, v[2 * q + 1] * down, h[q], l[q]);
+        o.hi = u32x4{h[0], h[1], h[2], h[3]};
+        o.lo = u32x4{l[0], l[1], l[2], l[3]};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o.up[q] = __shfl(up, 4 * g + q, 64);
+        return o;
+    };
+    // B's columns at and past the rank count as zero (t's are, but 0 x inf)
+    auto rank_step = [&](const TOp& o, u32x4 bw, int kr, int rank, f32x4& acc) {
+        const int k = kr + 8 * g;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t v = bw[q];
+            const uint32_t lo = k + 2 * q < rank ? v & 0xffffu : 0u;
+            const uint32_t hi = k + 2 * q + 1 < rank ? v & 0xffff0000u : 0u;
+            bw[q] = lo | hi;
+        }
+        const f32x4 pp = mfma(o.lo, bw, mfma(o.hi, bw, fzero));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = fmaf(o.up[q], pp[q], acc[q]);
+    };
+
+    Pos lp, cp;
+    lp.ae = ae0;
+    lp.li = 0;
+    while (true) {                                // the segment of `beg`
+        enter(lp);
+        if (lp.lo < lp.hi) break;
+        ++lp.li;
+    }
+    cp = lp;
+    load_x(cp);
+    load_segment(lp);
+    Tile ring[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        load_tile(lp, ring[d]);
+        if (!over(lp) && advance(lp) && !over(lp)) load_segment(lp);
+    }
+    int rank = rank_of(cp.ae, cp.li);
+    TOp t0{zero, zero, fzero};
+    if (32 * kw < rank) t0 = t_operand(a.lin[cp.li], rank, 32 * kw);
+    int par = 0;
+    // Past the end of the list a step only keeps the pipeline's shape: a way
+    // out of the middle of the unrolled loop would join its head in the
+    // structured control flow, with this tile's loads the youngest, and every
+    // round would drain all loads in flight.
+    auto do_step = [&](Tile& t) {
+        const bool live = !over(cp);
+        const MoeLin& L = a.lin[cp.li];
+        const bool pre = rank_rows_aligned(L) && 32 * kw < rank;
+        f32x4 acc = fzero;
+        if (live) {
+#pragma unroll
+            for (int b = 0; b < NBK; ++b) {
+                uint32_t w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { const uint32_t v = t.w[b][q]; w[q] = v; }
+                if constexpr (GPB > 1) transpose_words(w);
+#pragma unroll
+                for (int q = 0; q < GPB; ++q) {
+                    constexpr int four = 4;
+                    const int p = GPB * b + q;
+                    const uint32_t sz = __builtin_amdgcn_ds_bpermute(from + 64 * (p % four),
+                                                                     t.s[p / four] | (t.z[p / four] << 16));
+                    const Zq zq = make_zq(sz >> 16);
+                    f32x4 pp = mfma(x[b][SPG * q], codes_minus_zero(w[SPG * q], zq, mlo, mhi, bias), fzero);
+#pragma unroll
+                    for (int u = SPG * q + 1; u < SPG * q + SPG; ++u)
+                        pp = mfma(x[b][u], codes_minus_zero(w[u], zq, mlo, mhi, bias), pp);
+                    const bool on = (kb0 + b) * 128 + 32 * SPG * q < K;
+                    acc = fma4(on ? f16_bits_to_f32(static_cast<uint16_t>(sz)) : 0.f, pp, acc);
+                }
+            }
+            if (pre) rank_step(t0, t.b, 32 * kw, rank, acc);
+        }
+        load_tile(lp, t);
+        if (!over(lp) && advance(lp) && !over(lp)) load_segment(lp);
+        const int tile = cp.t + rw;
+        const int row = 16 * tile + r;
+        const bool rowv = live && tile < cp.hi && row < L.d_out;
+        // rank steps that were not prefetched: past 32 KW columns, or rows of
+        // B that are not 16-byte aligned
+        for (int kr = 32 * (pre ? kw + KW : kw); kr < (live ? rank : 0); kr += 32 * KW) {
+            const TOp o = kr == 32 * kw ? t0 : t_operand(L, rank, kr);
+            const uint16_t* brow = L.B + static_cast<size_t>(of(v_e, cp.ae)) * L.b_stride +
+                                   static_cast<size_t>(min(row, L.d_out - 1)) * L.r_max;
+            u32x4 bw;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int k = kr + 8 * g + 2 * q;
+                const uint32_t lo = brow[k < L.r_max ? k : 0], hi = brow[k + 1 < L.r_max ? k + 1 : 0];
+                bw[q] = lo | (hi << 16);
+            }
+            rank_step(o, bw, kr, rank, acc);
+        }
+        // the K parts summed in order: wave kw takes the slots 4 g + QN kw ..
+        // of the tile.  Buffer stores, whose bounds check drops the absent
+        // slots and rows: with a branch around them the compiler would have
+        // to count them as not issued and wait for younger loads instead.
+        constexpr int QN = KW >= 4 ? 1 : 4 / KW;
+        const int q0 = KW > 1 ? QN * kw : 0;
+        float v[QN];
+        if constexpr (KW > 1) {
+            float* const rb = red + (par * waves + rw * KW) * 256;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) rb[kw * 256 + q * 64 + lane] = acc[q];
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < QN; ++q) {
+                v[q] = rb[((q0 + q) & 3) * 64 + lane];
+#pragma unroll
+                for (int u = 1; u < KW; ++u) v[q] += rb[u * 256 + ((q0 + q) & 3) * 64 + lane];
+            }
+            par ^= 1;
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = acc[q];
+        }
+        const int scnt = of(v_scnt, min(cp.ae, elast));
+#pragma unroll
+        for (int q = 0; q < QN; ++q) {
+            const bool on = rowv && q0 + q < 4 && cp.p0 + 4 * g + q0 + q < scnt;
+            const int os = KW == 1 ? osl[q] : KW == 2 ? (kw ? osl[2 + q] : osl[q]) : osl_k;
+            if (L.d_out <= kStreamMaxRows)
+                buffer_store_out(L.y, static_cast<uint32_t>(a.T * a.k) * L.d_out, on ? os * L.d_out + row : -1, v[q],
+                                 a.out);
+            else if (on)
+                store_out(L.y, static_cast<size_t>(os) * L.d_out + row, v[q], a.out);
+        }
+        const int ae = cp.ae, p0 = cp.p0;
+        if (live && advance(cp) && !over(cp)) {
+            if (cp.ae != ae || cp.p0 != p0) load_x(cp);
+            rank = rank_of(cp.ae, cp.li);
+            if (32 * kw < rank) t0 = t_operand(a.lin[cp.li], rank, 32 * kw);
+            // wait here, once per segment: x pending where the paths meet
+            // would make every step wait for all loads in flight
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        }
+    };
+    while (!over(cp)) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) do_step(ring[d]);
+    }
+}
+
 // Many slots per expert, 4-bit codes: the expert's rows against its slots on
 // MFMA (v_mfma_f32_16x16x32_f16), so the per-slot VALU work of the kernel
 // above (every slot's dot products on every lane) becomes MFMA rows.
@@ -1246,6 +1627,26 @@ hipError_t launch_direct(const MoeArgs& a, int lg, int cpl, int nb, int qx, int 
     return launch_direct3<64, 2, 8>(a, nb, blocks, st);
 }
 
+template <int NBK, int KW>
+hipError_t launch_stream2(const MoeArgs& a, int blocks, hipStream_t st) {
+    constexpr int waves = KW > 4 ? KW : 4;
+    const dim3 grid(blocks), block(64 * waves);
+    const size_t lds = static_cast<size_t>(2) * waves * 256 * sizeof(float);
+    if (a.G % 128 == 0)
+        hipLaunchKernelGGL((moe_stream_kernel<NBK, 1, KW, kStreamDepth>), grid, block, lds, st, a);
+    else
+        hipLaunchKernelGGL((moe_stream_kernel<NBK, 2, KW, kStreamDepth>), grid, block, lds, st, a);
+    return hipGetLastError();
+}
+
+// Rows of nkb 128-code blocks: the fewest waves that leave each at most four.
+hipError_t launch_stream(const MoeArgs& a, int nkb, int blocks, hipStream_t st) {
+    if (nkb > 16) return nkb <= 24 ? launch_stream2<3, 8>(a, blocks, st) : launch_stream2<4, 8>(a, blocks, st);
+    if (nkb > 8) return nkb <= 12 ? launch_stream2<3, 4>(a, blocks, st) : launch_stream2<4, 4>(a, blocks, st);
+    if (nkb > 4) return nkb <= 6 ? launch_stream2<3, 2>(a, blocks, st) : launch_stream2<4, 2>(a, blocks, st);
+    return nkb <= 2 ? launch_stream2<2, 1>(a, blocks, st) : launch_stream2<4, 1>(a, blocks, st);
+}
+
 }  // namespace
 
 bool moe_fits(const QW& w, int E, int T, int k) {
@@ -1303,6 +1704,10 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
     // (tiles of 16 rows), 2-bit codes are unpacked once per batch
     const bool many = S >= 2 * max_active;
     const bool on_mfma = many && bits == 4;
+    // the streamed kernel: see its comment for where the line lies
+    const int nkb = (d_in + 127) / 128;
+    const bool stream = bits == 4 && nkb <= 32 && w[0].G % 64 == 0 && max_active >= kStreamMinExperts &&
+                        max_active * d_in >= kStreamMinWidth;
     int prep_end = 0, blk_end = 0;
     for (int i = 0; i < n; ++i) {
         MoeLin& L = a.lin[i];
@@ -1318,10 +1723,11 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
         L.r_max = r_max[i];
         L.rq = r_max[i] > 0 ? (r_max[i] + 3) / 4 : 1;
         const int rgroups = (w[i].d_out + rows_per_wave(bits) - 1) / rows_per_wave(bits);
-        L.bpe = on_mfma ? (w[i].d_out + 16 * kMoeTpw - 1) / (16 * kMoeTpw)
-                        : (rgroups + rg_per_block - 1) / rg_per_block;
+        L.bpe = stream ? (w[i].d_out + 15) / 16
+                       : on_mfma ? (w[i].d_out + 16 * kMoeTpw - 1) / (16 * kMoeTpw)
+                                 : (rgroups + rg_per_block - 1) / rg_per_block;
         prep_end += max_active * L.rq;
-        blk_end += max_active * L.bpe;
+        blk_end += stream ? L.bpe : max_active * L.bpe;       // streamed: tiles per expert
         L.prep_end = prep_end;
         L.blk_end = blk_end;
     }
@@ -1372,6 +1778,11 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
         hipLaunchKernelGGL(moe_prep_kernel<2>, dim3(pgrid), dim3(256), plds, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (stream) {
+        const int blocks = static_cast<int>(min(static_cast<long long>(nkb > 16 ? kStreamBlocks / 2 : kStreamBlocks),
+                                                static_cast<long long>(max_active) * blk_end));
+        return launch_stream(a, nkb, blocks, st);
+    }
     if (on_mfma) {
         const size_t lds = static_cast<size_t>(2) * 16 * kMoeTpw * szl_stride(d_in / w[0].G) * 2;
         // quantization groups a 128-code block can meet (see the kernel)

@@ -533,3 +533,74 @@ def test_gate_up_window_into_gated_down(T, k):
     assert_oracle(out_to_numpy(y), ref, extra=extra)
     chain = _full_ref(Q, s, z, A, B, ranks, linear.silu(refs[0]) * refs[1], ids, True, bits, G, d_in)
     assert rel_l2(out_to_numpy(y), chain) <= REL_L2_TOL
+
+
+@pytest.mark.parametrize("d_in,G,d_out,r_max,E,T,k,x_per_slot", [
+    (256, 128, 100, 8, 160, 40, 8, False),      # one wave per row tile, two blocks
+    (512, 256, 33, 20, 80, 12, 8, True),        # rank rows not 16-byte aligned
+    (768, 64, 130, 40, 56, 9, 8, True),         # two waves of three blocks, two groups per block
+    (832, 64, 16, 72, 64, 64, 8, False),        # a last block of half a group, rank steps past the prefetched
+    (2048, 128, 333, 33, 40, 8, 5, False),      # four waves of four blocks
+    (1472, 64, 48, 0, 64, 16, 8, False),        # four waves of three, no factors
+    (2944, 128, 65, 256, 36, 64, 8, True),      # eight waves of three, 16 slots an expert and more
+    (4096, 512, 40, 16, 32, 9, 4, False),       # eight waves of four
+])
+@pytest.mark.parametrize("dyn", [False, True])
+def test_streamed_experts(d_in, G, d_out, r_max, E, T, k, x_per_slot, dyn):
+    """The streamed kernel at the edges of its instances: ragged row tiles,
+    partial K blocks, every number of K waves, ranks off 8 and past one step,
+    one slot, several and several passes of 16 slots on an expert, an expert
+    id out of range, per-slot ranks."""
+    Q, s, z, A, B = _oracle_experts(E, d_out, d_in, 4, G, r_max, 60 + d_in, svd=False)
+    ranks = wl.moe_expert_ranks(60, 0, 0, E, levels=sorted({0, r_max // 3, r_max})) if r_max else np.zeros(E, np.int32)
+    ids, wts = wl.routing(T, 61, 0, E, k)
+    ids = ids.copy()
+    ids[:T // 3, 0] = 5                                       # a busy expert
+    ids[T - 1, 0] = E
+    x = wl.activation((T, k, d_in) if x_per_slot else (T, d_in), 62, 0, 1, dtype="bf16")
+    ex = _device_experts(Q, s, z, A, B, ranks, d_out, d_in, 4, G, r_max)
+    idd = torch.from_numpy(ids).cuda()
+    sr = None
+    slot_ranks = np.asarray(ranks)[np.minimum(ids, E - 1)]
+    if dyn:
+        slot_ranks = np.random.default_rng(d_in).integers(0, r_max + 1, ids.shape).astype(np.int32)
+        sr = [torch.from_numpy(slot_ranks).cuda()]
+    y = cl.moe_linear_decode_window([ex], dev_u16(x.bits, torch.bfloat16), idd, out_dtype=torch.float32,
+                                    slot_ranks=sr)[0]
+    got = out_to_numpy(y)
+    assert not got[T - 1, 0].any()
+    X = x.values if x_per_slot else np.repeat(x.values[:, None], k, 1)
+    ref = np.zeros(got.shape)
+    for t in range(T):
+        for j in range(k):
+            e = ids[t, j]
+            if e < E:
+                W = quant.dequant_packed(Q[e], s[e], z[e], 4, G, d_in)
+                r = slot_ranks[t, j]
+                ref[t, j] = W @ X[t, j] + B[e][:, :r].astype(np.float64) @ (A[e][:r].astype(np.float64) @ X[t, j])
+    with pytest.raises(cl.ClError):
+        cl.moe_status()
+    # fp32 sums of d_in products and r_max factor terms, t to 2^-22
+    assert rel_l2(got, ref) <= 2.0 ** -22 + 2.0 ** -24 * np.sqrt(d_in)
+
+
+def test_streamed_experts_keep_large_and_small_factor_products():
+    """t = A x beyond fp16's largest value (one token) and far below its
+    subnormal range (another): the streamed kernel scales each slot's t by a
+    power of two."""
+    E, T, k, d_in, d_out, r_max = 40, 8, 8, 1024, 48, 16
+    Q, s, z, A, B = _oracle_experts(E, d_out, d_in, 4, 128, r_max, 70, svd=False)
+    A = (A.astype(np.float64) * 5e4).astype(np.float16)
+    ids, _ = wl.routing(T, 71, 0, E, k)
+    x = wl.activation((T, d_in), 72, 0, 1)
+    xv = x.values.copy()
+    xv[3] = (xv[3] * 2.0 ** -20).astype(np.float16).astype(np.float64)
+    ranks = np.full(E, r_max, np.int32)
+    ex = _device_experts(Q, s, z, A, B, ranks, d_out, d_in, 4, 128, r_max)
+    y = cl.moe_linear_decode(ex, torch.from_numpy(xv.astype(np.float16)).cuda(), torch.from_numpy(ids).cuda(),
+                             out_dtype=torch.float32)
+    got = out_to_numpy(y)
+    ref = _full_ref(Q, s, z, A, B, ranks, xv, ids, False, 4, 128, d_in)
+    assert np.abs(xv[0] @ A[ids[0, 0]].astype(np.float64).T).max() > 65504
+    for t in range(T):
+        assert rel_l2(got[t], ref[t]) <= 2.0 ** -22 + 2.0 ** -24 * np.sqrt(d_in)
