@@ -12,10 +12,9 @@
 //     X' = X as fp16 (bf16 converted) with every 8 consecutive k reordered
 //     (k0,k4,k1,k5,k2,k6,k3,k7): the order in which the code unpack below
 //     produces weights, so the contraction is unchanged.
-//  2. prefill_kernel: 128 x 256 output tiles (tokens x weight rows; 128 x 128
-//     when 256-row tiles would leave CUs without two workgroups: 4096 x 4096
-//     at M = 2048 went from 133 to 117 us, while 14336 x 4096 stays faster
-//     with 256 rows, 322 against 350 us), K in steps of 128 codes.  X' tiles
+//  2. prefill_kernel: 128 x 256 output tiles (tokens x weight rows; smaller
+//     ones, with K split between the waves of a workgroup, where those would
+//     leave CUs idle: see prefill_tile), K in steps of 128 codes.  X' tiles
 //     go from global memory straight into LDS (global_load_lds, 16 bytes per
 //     lane, two 32 KB stages, chunks XOR-swizzled by row so the MFMA operand
 //     reads are bank-conflict free).  Each of the four waves owns 128 tokens
@@ -280,11 +279,15 @@ struct WStep {
     uint32_t w[BITS];        // 32 codes = BITS words
 };
 
-template <int BITS, int JT>
-__global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
+// LDS of one set of four waves, in 16-byte units: two stages of X', two
+// windows of 8 groups of scales and zeros.
+__host__ __device__ constexpr int prefill_set_lds(int mt, int jt) { return 2 * 16 * mt * 16 + 64 * jt * 4; }
+
+template <int BITS, int JT, int MT, int KS>
+__global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(PrefillArgs a) {
     // MT token tiles and JT row tiles of 16 per wave: the workgroup covers
-    // BM = 16 MT tokens x 64 JT weight rows
-    constexpr int MT = 8;
+    // BM = 16 MT tokens x 64 JT weight rows with KS sets of four waves, each
+    // on its own run of K steps
     constexpr int BM = 16 * MT;
     constexpr int BNT = 64 * JT;
     // LDS (dynamic, prefill_lds_bytes): two stages of X', [BM rows][16
@@ -294,10 +297,12 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     // (a lane's read of its row's value is then one of 16 consecutive 2-byte
     // entries: no bank conflicts, where [row][8] had 16-byte strides)
     extern __shared__ u32x4 smem[];
-    u32x4 (*xs)[BM * 16] = reinterpret_cast<u32x4 (*)[BM * 16]>(smem);
-    uint16_t (*szw)[2][8][BNT] = reinterpret_cast<uint16_t (*)[2][8][BNT]>(smem + 2 * BM * 16);
+    const int set = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+    u32x4* const lds = smem + set * prefill_set_lds(MT, JT);
+    u32x4 (*xs)[BM * 16] = reinterpret_cast<u32x4 (*)[BM * 16]>(lds);
+    uint16_t (*szw)[2][8][BNT] = reinterpret_cast<uint16_t (*)[2][8][BNT]>(lds + 2 * BM * 16);
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x & 255;     // within the set
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4;               // lane group: k sub-block of an MFMA step
@@ -307,6 +312,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     const int nb = blockIdx.x / a.mblocks;
     const int m0 = mb * BM, n0 = nb * BNT + wave * 16 * JT;
     const int nk = (a.K + BK - 1) / BK;
+    const int nit = (nk + KS - 1) / KS;    // steps per set; the last sets may have fewer
+    const int k_beg = set * nit, k_end = min(nk, k_beg + nit);
     const int groups = a.K / a.G;
     const int words_row = a.K * BITS / 32;
 
@@ -520,35 +527,54 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     // the barrier before) and is complete at the barrier after
     const int nwnd = (groups + 7) / 8;
     WStep<BITS> wa[JT], wb[JT];
-    load_x(0, 0);
-    load_w(0, wa);
-    fetch_sz(0);
-    store_sz(0);
+    if (k_beg < k_end) {
+        load_x(k_beg, 0);
+        load_w(k_beg, wa);
+        fetch_sz(k_beg / spw);
+        store_sz(k_beg / spw);
+    }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     // step k: the window after the current one is fetched at the window's
-    // first step and stored at its end (its buffer's previous window retired
-    // at the barrier before the fetch; the barrier after the store publishes
-    // it)
-    {
-    for (int kb = 0; kb < nk; kb += 2) {
-        const bool f0 = kb % spw == 0 && kb / spw + 1 < nwnd;
-        if (f0) fetch_sz(kb / spw + 1);
-        if (kb + 1 < nk) { load_x(kb + 1, 1); load_w(kb + 1, wb); }
-        compute(kb, 0, wa);
-        if (f0) store_sz(kb / spw + 1);
+    // first step (or the set's) and stored at its end (its buffer's previous
+    // window retired at the barrier before the fetch; the barrier after the
+    // store publishes it)
+    auto step = [&](int kb, int st, const WStep<BITS> (&cur)[JT], WStep<BITS> (&next)[JT]) {
+        if (KS == 1 || kb < k_end) {
+            const bool f = (kb % spw == 0 || (KS > 1 && kb == k_beg)) && kb / spw + 1 < nwnd;
+            if (f) fetch_sz(kb / spw + 1);
+            if (kb + 1 < k_end) { load_x(kb + 1, st ^ 1); load_w(kb + 1, next); }
+            compute(kb, st, cur);
+            if (f) store_sz(kb / spw + 1);
+        }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        if (kb + 1 >= nk) break;
-        const bool f1 = (kb + 1) % spw == 0 && (kb + 1) / spw + 1 < nwnd;
-        if (f1) fetch_sz((kb + 1) / spw + 1);
-        if (kb + 2 < nk) { load_x(kb + 2, 0); load_w(kb + 2, wa); }
-        compute(kb + 1, 1, wb);
-        if (f1) store_sz((kb + 1) / spw + 1);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
+    };
+    for (int it = 0; it < nit; it += 2) {
+        step(k_beg + it, 0, wa, wb);
+        if (it + 1 >= nit) break;
+        step(k_beg + it + 1, 1, wb, wa);
     }
 
+    // the sets' sums meet in LDS (the X' stages are free), in set order
+    if constexpr (KS > 1) {
+        if (set > 0) {
+            f32x4* dst = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < JT; ++j) dst[(i * JT + j) * 256 + tid] = acc[i][j];
+        }
+        __syncthreads();
+        if (set > 0) return;
+#pragma unroll
+        for (int u = 1; u < KS; ++u) {
+            const f32x4* src = reinterpret_cast<const f32x4*>(smem + u * prefill_set_lds(MT, JT));
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < JT; ++j) acc[i][j] += src[(i * JT + j) * 256 + tid];
+        }
     }
 
     // ---- rank-r correction: MFMA steps of 32 over [T | B] (natural k order)
@@ -606,13 +632,50 @@ int prefill_cus() {
     return cus[dev];
 }
 
-// Row tiles per wave: 256-row workgroup tiles, or 128-row ones when 256-row
-// tiles would not give every CU two workgroups (4096 x 4096 at M = 2048:
-// 256 tiles; 117 against 133 us, while 14336 x 4096 stays faster with 256
-// rows, 322 against 350 us)
-int prefill_jt(int M, int N) {
-    const long long tiles256 = static_cast<long long>((M + 127) / 128) * ((N + 255) / 256);
-    return tiles256 < 2ll * prefill_cus() ? 2 : 4;
+// Workgroup tile (64 jt weight rows x 16 mt tokens) and sets of four waves
+// that split K.  Large problems take 256-row tiles, or 128-row ones when
+// 256-row tiles would not give every CU two workgroups (4096 x 4096 at M =
+// 2048: 117 against 133 us, while 14336 x 4096 stays faster with 256 rows, 322
+// against 350 us).  Where 128 x 128 tiles leave CUs idle or with one wave per
+// SIMD, smaller tiles with K split inside the workgroup fill the chip (a K
+// step of a lone workgroup waits for its loads; the tile's dequantization is
+// shared by fewer tokens, which idle CUs pay for).  Per call, 4 bits, rank 32,
+// 4096 x 4096 at M = 64 / 200 / 333 / 512 / 768 / 1024:
+//   128 x 128          56.8  59.4  59.4  59.8  61.6  62.8 us
+//   64 x 128, 2 sets   40.9  39.0  40.9  42.6  55.5  58.9
+//   128 x 64, 2 sets   37.0  37.8  38.6  41.1  68.8  71.1
+//   64 x 64, 4 sets    28.9  29.9  46.2  48.8  67.3  83.4
+// 14336 x 4096 at M = 64 / 128 / 200 / 333: 56.2 58.8 60.6 75.9, 38.8 41.2 57.2
+// 79.9, 37.4 38.4 67.2 95.7, 29.1 45.9 82.4 119.  So: the smallest tile while
+// one of them per CU holds the problem, then 128 x 64, then 64 x 128 up to two
+// per CU.
+struct PrefillTile {
+    int jt, mt, ks;
+};
+
+PrefillTile prefill_tile(int M, int N) {
+    auto tiles = [&](int m, int n) { return static_cast<long long>((M + m - 1) / m) * ((N + n - 1) / n); };
+    const int cus = prefill_cus();
+    if (tiles(64, 64) <= cus) return {1, 4, 4};
+    if (tiles(128, 64) <= cus) return {1, 8, 2};
+    if (tiles(64, 128) <= 2 * cus) return {2, 4, 2};
+    return tiles(128, 256) < 2 * cus ? PrefillTile{2, 8, 1} : PrefillTile{4, 8, 1};
+}
+
+template <int BITS, int JT, int MT, int KS>
+void launch_prefill_tile(const PrefillArgs& a, hipStream_t st) {
+    const unsigned blocks = static_cast<unsigned>(a.mblocks) * ((a.N + 64 * JT - 1) / (64 * JT));
+    hipLaunchKernelGGL((prefill_kernel<BITS, JT, MT, KS>), dim3(blocks), dim3(256 * KS),
+                       KS * prefill_set_lds(MT, JT) * sizeof(u32x4), st, a);
+}
+
+template <int BITS>
+void launch_prefill(const PrefillTile& t, const PrefillArgs& a, hipStream_t st) {
+    if (t.jt == 4) launch_prefill_tile<BITS, 4, 8, 1>(a, st);
+    else if (t.jt == 2 && t.mt == 8) launch_prefill_tile<BITS, 2, 8, 1>(a, st);
+    else if (t.jt == 2) launch_prefill_tile<BITS, 2, 4, 2>(a, st);
+    else if (t.mt == 8) launch_prefill_tile<BITS, 1, 8, 2>(a, st);
+    else launch_prefill_tile<BITS, 1, 4, 4>(a, st);
 }
 
 }  // namespace
@@ -642,8 +705,8 @@ hipError_t launch_linear_prefill(const QW& w, const LR& c, const void* X, int M,
     a.M = M; a.N = w.d_out; a.K = w.d_in; a.G = w.G;
     a.rank = c.rank; a.r_max = c.r_max; a.r_pad = (c.rank + 31) / 32 * 32;
     a.out = out;
-    const int jt = prefill_jt(M, w.d_out);
-    a.mblocks = (M + 127) / 128;
+    const PrefillTile t = prefill_tile(M, w.d_out);
+    a.mblocks = (M + 16 * t.mt - 1) / (16 * t.mt);
     const uint16_t* Xa = static_cast<const uint16_t*>(X);
     if (c.rank > 0) {
         const int mtiles = (M + XT_M - 1) / XT_M, parts = xt_parts(w.d_in);
@@ -661,16 +724,9 @@ hipError_t launch_linear_prefill(const QW& w, const LR& c, const void* X, int M,
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const unsigned blocks = static_cast<unsigned>(a.mblocks * ((w.d_out + 64 * jt - 1) / (64 * jt)));
-    const dim3 grid(blocks), block(256);
-    // X' stages and scale/zero windows (see prefill_kernel)
-    const size_t lds = (2 * 128 * 16 + 64 * jt * 4) * sizeof(u32x4);
-    if (w.bits == 4 && jt == 4) hipLaunchKernelGGL((prefill_kernel<4, 4>), grid, block, lds, st, a);
-    else if (w.bits == 4) hipLaunchKernelGGL((prefill_kernel<4, 2>), grid, block, lds, st, a);
-    else if (w.bits == 3 && jt == 4) hipLaunchKernelGGL((prefill_kernel<3, 4>), grid, block, lds, st, a);
-    else if (w.bits == 3) hipLaunchKernelGGL((prefill_kernel<3, 2>), grid, block, lds, st, a);
-    else if (jt == 4) hipLaunchKernelGGL((prefill_kernel<2, 4>), grid, block, lds, st, a);
-    else hipLaunchKernelGGL((prefill_kernel<2, 2>), grid, block, lds, st, a);
+    if (w.bits == 4) launch_prefill<4>(t, a, st);
+    else if (w.bits == 3) launch_prefill<3>(t, a, st);
+    else launch_prefill<2>(t, a, st);
     return hipGetLastError();
 }
 

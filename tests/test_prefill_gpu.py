@@ -223,3 +223,30 @@ def test_prefill_half_k_step(bits, G, d_in):
     ref = linear.forward_packed(Q, s, z, bits, G, A, B, rank, x.values)
     W_hat = quant.dequant_packed(Q, s, z, bits, G, d_in)
     assert_oracle(out_to_numpy(y), ref, extra=fp16_tile_bound(W_hat, x.values, A, B, rank))
+
+
+@pytest.mark.parametrize("M,d_out", [
+    (65, 100),        # 64 x 64 tiles, four K sets
+    (300, 3400),      # 128 tokens x 64 rows, two sets
+    (700, 3000),      # 64 tokens x 128 rows, two sets
+    (1100, 3700),     # 128 x 128
+    (2100, 8000),     # 128 tokens x 256 rows
+])
+@pytest.mark.parametrize("bits,G,d_in", [
+    (4, 64, 64),      # half a K step: sets without one
+    (4, 32, 1312),    # 11 steps over the sets, the last a quarter; windows of two steps
+    (2, 64, 320), (3, 32, 640), (4, 256, 768),
+])
+def test_prefill_every_tile(M, d_out, bits, G, d_in):
+    """Each tile of the dispatch with K that does not divide into its sets,
+    scale windows that begin inside a set's run, ragged tokens and rows."""
+    if d_in % 64:
+        d_in = d_in // 64 * 64 + 64
+    w, (Q, s, z, A, B) = _layer(d_out, d_in, bits, G, 40, M + bits)
+    c = cl.LowRank(dev_f16(A), dev_f16(B), 40, 33)
+    x = wl.activation((M, d_in), 24, M, d_out)
+    y = cl.linear_prefill(w, c, dev_u16(x.bits, torch.float16), out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = linear.forward_packed(Q, s, z, bits, G, A, B, 33, x.values)
+    W_hat = quant.dequant_packed(Q, s, z, bits, G, d_in)
+    assert_oracle(out_to_numpy(y), ref, extra=fp16_tile_bound(W_hat, x.values, A, B, 33))
