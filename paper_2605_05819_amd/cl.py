@@ -9,6 +9,7 @@ library to load instead (the host-sanitized build, for instance).
 
 import ctypes
 import os
+import struct
 from dataclasses import dataclass
 from typing import Optional
 
@@ -117,8 +118,25 @@ def lib():
         for name, (res, args) in _SIGNATURES.items():
             fn = getattr(handle, name)
             fn.restype, fn.argtypes = res, args
+        # The same entry points for packed descriptors (bytes in place of
+        # ctypes structures), which cost a fraction of the structures to make.
+        for name in _PACKED:
+            fn = handle[name]
+            res, args = _SIGNATURES[name]
+            fn.restype = res
+            fn.argtypes = [a if a in (ctypes.c_int32, ctypes.c_size_t) else ctypes.c_void_p for a in args]
+            _packed[name] = fn
         _lib = handle
     return _lib
+
+
+_PACKED = ("cl_linear_decode", "cl_linear_decode_noalloc", "cl_linear_decode_window", "cl_linear_decode_glu",
+           "cl_linear_prefill", "cl_linear_workspace", "cl_linear_window_workspace", "cl_prefill_workspace")
+_packed = {}
+
+
+def _call(name):
+    return _packed.get(name) or (lib() and _packed[name])
 
 
 def _check(status):
@@ -146,10 +164,16 @@ class _Checked(list):
 
     def on_gpu(self):
         for name, t in self:
-            _need(t.device.type == "cuda", "%s must be on the GPU (got %s)" % (name, t.device))
+            if not t.is_cuda:
+                raise ValueError("%s must be on the GPU (got %s)" % (name, t.device))
 
 
 def _dev_tensor(t, name, dtypes, shape=None, chk=None):
+    if isinstance(t, torch.Tensor) and t.dtype in dtypes and (shape is None or t.shape == shape) and \
+            t.is_contiguous() and (chk is not None or t.is_cuda):
+        if chk is not None:
+            chk.append((name, t))
+        return
     _need(isinstance(t, torch.Tensor), "%s must be a torch.Tensor" % name)
     _need(t.dtype in dtypes, "%s must have dtype %s (got %s)" % (name, " or ".join(map(str, dtypes)), t.dtype))
     _need(t.is_contiguous(), "%s must be contiguous" % name)
@@ -197,10 +221,21 @@ def _check_ws(ws, need, chk, name="ws"):
     _need(ws.numel() >= need, "%s holds %d bytes, %d needed" % (name, ws.numel(), need))
 
 
-def _stream(stream):
+def _raw_stream(stream):
+    """The hipStream_t of ``stream``, or of the current device's current one."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
+
+
+def _stream(stream):
+    return ctypes.c_void_p(_raw_stream(stream))
+
+
+_PACK_QW = struct.Struct("PPPiiii").pack
+_PACK_LR = struct.Struct("PPii").pack
 
 
 @dataclass
@@ -215,6 +250,11 @@ class QWeight:
     bits: int
     group_size: int
 
+    def packed(self):
+        """The bytes of a cl_qweight."""
+        return _PACK_QW(self.q.data_ptr(), self.scales.data_ptr(), self.zeros.data_ptr(), self.d_out, self.d_in,
+                        self.bits, self.group_size)
+
     def c(self):
         return QWeightC(self.q.data_ptr(), self.scales.data_ptr(), self.zeros.data_ptr(),
                         self.d_out, self.d_in, self.bits, self.group_size)
@@ -228,6 +268,11 @@ class LowRank:
     B: Optional[torch.Tensor]
     r_max: int
     rank: int
+
+    def packed(self):
+        """The bytes of a cl_lowrank."""
+        return _PACK_LR(0 if self.A is None else self.A.data_ptr(), 0 if self.B is None else self.B.data_ptr(),
+                        self.r_max, self.rank)
 
     def c(self):
         return LowRankC(0 if self.A is None else self.A.data_ptr(),
@@ -254,9 +299,7 @@ def dequantize(w, stream=None):
 
 
 def linear_workspace(w, c, tokens):
-    qc = w.c()
-    lc = c.c() if c is not None else None
-    return lib().cl_linear_workspace(ctypes.byref(qc), ctypes.byref(lc) if lc else None, tokens)
+    return _call("cl_linear_workspace")(w.packed(), None if c is None else c.packed(), tokens)
 
 
 def workspace(nbytes, device):
@@ -277,15 +320,13 @@ def linear_decode(w, c, x, out_dtype=torch.float16, y=None, ws=None, stream=None
         y = torch.empty((T, w.d_out), dtype=out_dtype, device=x.device)
     _dev_tensor(y, "y", _OUT, (T, w.d_out), chk)
     chk.on_gpu()
-    need = linear_workspace(w, c, T)
+    qb, lb = w.packed(), None if c is None else c.packed()
+    need = _call("cl_linear_workspace")(qb, lb, T)
     if ws is None:
         ws = workspace(need, x.device)
     _check_ws(ws, need, None)
-    qc = w.c()
-    lc = c.c() if c is not None else None
-    _check(lib().cl_linear_decode(ctypes.byref(qc), ctypes.byref(lc) if lc else None, _ptr(x), T,
-                                  _DTYPE_CODE[x.dtype], _ptr(y), _DTYPE_CODE[y.dtype], _ptr(ws),
-                                  0 if ws is None else ws.numel(), _stream(stream)))
+    _check(_call("cl_linear_decode")(qb, lb, x.data_ptr(), T, _DTYPE_CODE[x.dtype], y.data_ptr(), _DTYPE_CODE[y.dtype],
+                                     ws.data_ptr(), ws.numel(), _raw_stream(stream)))
     return y
 
 
@@ -303,25 +344,26 @@ def linear_decode_noalloc(w, c, x, out_dtype=torch.float16, y=None, stream=None)
         y = torch.empty((T, w.d_out), dtype=out_dtype, device=x.device)
     _dev_tensor(y, "y", _OUT, (T, w.d_out), chk)
     chk.on_gpu()
-    qc = w.c()
-    lc = c.c() if c is not None else None
-    _check(lib().cl_linear_decode_noalloc(ctypes.byref(qc), ctypes.byref(lc) if lc else None, _ptr(x), T,
-                                          _DTYPE_CODE[x.dtype], _ptr(y), _DTYPE_CODE[y.dtype], _stream(stream)))
+    _check(_call("cl_linear_decode_noalloc")(w.packed(), None if c is None else c.packed(), x.data_ptr(), T,
+                                             _DTYPE_CODE[x.dtype], y.data_ptr(), _DTYPE_CODE[y.dtype],
+                                             _raw_stream(stream)))
     return y
 
 
-def _window_structs(ws_, cs):
-    n = len(ws_)
-    qa = (QWeightC * n)(*[w.c() for w in ws_])
-    la = None
+_NO_FACTORS = _PACK_LR(0, 0, 0, 0)
+
+
+def _window_packed(ws_, cs):
+    """The descriptor arrays of a window as bytes."""
+    lb = None
     if cs is not None and any(c is not None for c in cs):
-        la = (LowRankC * n)(*[(c.c() if c is not None else LowRankC(0, 0, 0, 0)) for c in cs])
-    return qa, la
+        lb = b"".join([c.packed() if c is not None else _NO_FACTORS for c in cs])
+    return b"".join([w.packed() for w in ws_]), lb
 
 
 def window_workspace(ws_, cs, tokens):
-    qa, la = _window_structs(ws_, cs)
-    return lib().cl_linear_window_workspace(len(ws_), qa, la, tokens)
+    qb, lb = _window_packed(ws_, cs)
+    return _call("cl_linear_window_workspace")(len(ws_), qb, lb, tokens)
 
 
 def linear_decode_window(ws_, cs, x, out_dtype=torch.float16, ys=None, ws=None, stream=None):
@@ -344,14 +386,14 @@ def linear_decode_window(ws_, cs, x, out_dtype=torch.float16, ys=None, ws=None, 
     for i, (w, y) in enumerate(zip(ws_, ys)):
         _dev_tensor(y, "ys[%d]" % i, _OUT, (T, w.d_out), chk)
     chk.on_gpu()
-    qa, la = _window_structs(ws_, cs)
-    need = lib().cl_linear_window_workspace(n, qa, la, T)
+    qb, lb = _window_packed(ws_, cs)
+    need = _call("cl_linear_window_workspace")(n, qb, lb, T)
     if ws is None:
         ws = workspace(need, x.device)
     _check_ws(ws, need, None)
-    yp = (ctypes.c_void_p * n)(*[y.data_ptr() for y in ys])
-    _check(lib().cl_linear_decode_window(n, qa, la, _ptr(x), T, _DTYPE_CODE[x.dtype], yp,
-                                         _DTYPE_CODE[ys[0].dtype], _ptr(ws), ws.numel(), _stream(stream)))
+    yp = struct.pack("%dP" % n, *[y.data_ptr() for y in ys])
+    _check(_call("cl_linear_decode_window")(n, qb, lb, x.data_ptr(), T, _DTYPE_CODE[x.dtype], yp,
+                                            _DTYPE_CODE[ys[0].dtype], ws.data_ptr(), ws.numel(), _raw_stream(stream)))
     return ys
 
 
@@ -370,13 +412,13 @@ def linear_decode_glu(gate_up, cs, x, out_dtype=torch.float16, h=None, ws=None, 
         h = torch.empty((T, gate_up[0].d_out), dtype=out_dtype, device=x.device)
     _dev_tensor(h, "h", _OUT, (T, gate_up[0].d_out), chk)
     chk.on_gpu()
-    qa, la = _window_structs(gate_up, cs)
-    need = lib().cl_linear_window_workspace(2, qa, la, T)
+    qb, lb = _window_packed(gate_up, cs)
+    need = _call("cl_linear_window_workspace")(2, qb, lb, T)
     if ws is None:
         ws = workspace(need, x.device)
     _check_ws(ws, need, None)
-    _check(lib().cl_linear_decode_glu(qa, la, _ptr(x), T, _DTYPE_CODE[x.dtype], _ptr(h), _DTYPE_CODE[h.dtype],
-                                      _ptr(ws), ws.numel(), _stream(stream)))
+    _check(_call("cl_linear_decode_glu")(qb, lb, x.data_ptr(), T, _DTYPE_CODE[x.dtype], h.data_ptr(),
+                                         _DTYPE_CODE[h.dtype], ws.data_ptr(), ws.numel(), _raw_stream(stream)))
     return h
 
 
@@ -407,9 +449,7 @@ def layer_sensitivity(D, K):
 
 
 def prefill_workspace(w, c, M):
-    qc = w.c()
-    lc = c.c() if c is not None else None
-    return lib().cl_prefill_workspace(ctypes.byref(qc), ctypes.byref(lc) if lc else None, M)
+    return _call("cl_prefill_workspace")(w.packed(), None if c is None else c.packed(), M)
 
 
 def linear_prefill(w, c, X, out_dtype=torch.float16, Y=None, ws=None, stream=None):
@@ -424,15 +464,14 @@ def linear_prefill(w, c, X, out_dtype=torch.float16, Y=None, ws=None, stream=Non
         Y = torch.empty((M, w.d_out), dtype=out_dtype, device=X.device)
     _dev_tensor(Y, "Y", _OUT, (M, w.d_out), chk)
     chk.on_gpu()
-    need = prefill_workspace(w, c, M)
+    qb, lb = w.packed(), None if c is None else c.packed()
+    need = _call("cl_prefill_workspace")(qb, lb, M)
     if ws is None and need:
         ws = workspace(need, X.device)
     _check_ws(ws, need, None)
-    qc = w.c()
-    lc = c.c() if c is not None else None
-    _check(lib().cl_linear_prefill(ctypes.byref(qc), ctypes.byref(lc) if lc else None, _ptr(X), M,
-                                   _DTYPE_CODE[X.dtype], _ptr(Y), _DTYPE_CODE[Y.dtype], _ptr(ws),
-                                   0 if ws is None else ws.numel(), _stream(stream)))
+    _check(_call("cl_linear_prefill")(qb, lb, X.data_ptr(), M, _DTYPE_CODE[X.dtype], Y.data_ptr(),
+                                      _DTYPE_CODE[Y.dtype], None if ws is None else ws.data_ptr(),
+                                      0 if ws is None else ws.numel(), _raw_stream(stream)))
     return Y
 
 
