@@ -404,9 +404,9 @@ size_t cl_moe_window_workspace(int32_t n, const cl_qweight* w_expert0, const int
  * nonlinearity between the gate/up and down windows of the cross-expert
  * reorganisation (Section 4.2.2; Appendix A.1, MoE Layer) is formed by the
  * down call: with few slots (the one-launch path of cl_moe_linear_decode) as
- * each workgroup reads its activations, otherwise by one small kernel that
- * writes h for every slot into the workspace ahead of the preparation and
- * backbone kernels.  Each h is computed in fp32, saturated at +-65504 and
+ * each workgroup reads its activations, otherwise by the preparation kernel
+ * or, for wide rows, by one small kernel that writes h for every slot into
+ * the workspace ahead of it.  Each h is computed in fp32, saturated at +-65504 and
  * rounded to fp16, the activation precision of every decode path.
  *
  *  g, u       device [T][k][d_in] of act_dtype (fp16 or bf16), 16-byte

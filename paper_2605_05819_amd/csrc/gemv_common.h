@@ -17,15 +17,15 @@ __device__ __forceinline__ void load8_f16(const uint16_t* p, int act, uint32_t o
 
 // Activations of one 16-byte chunk of codes, in the pair order of the
 // unpacked codes: word w, pair p = (x[w*CPW + p], x[w*CPW + p + CPW/2]).
-template <int BITS>
-__device__ __forceinline__ void load_chunk_x(const uint16_t* xr, int chunk, int act, f16x2* xv) {
+// load8(i, out): activations i .. i + 7 of the row as four f16x2 words.
+template <int BITS, typename F>
+__device__ __forceinline__ void load_chunk_pairs(int chunk, f16x2* xv, F load8) {
     constexpr int CPW = 32 / BITS, HPW = CPW / 2;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        const uint16_t* p = xr + (chunk * 4 + w) * CPW;
         uint32_t u[CPW / 2];                        // CPW halves as packed pairs
 #pragma unroll
-        for (int j = 0; j < CPW / 8; ++j) load8_f16(p + 8 * j, act, u + 4 * j);
+        for (int j = 0; j < CPW / 8; ++j) load8((chunk * 4 + w) * CPW + 8 * j, u + 4 * j);
         // u[i] holds (x[2i], x[2i+1]); pair p needs (x[p], x[p + HPW])
 #pragma unroll
         for (int pp = 0; pp < HPW; ++pp) {
@@ -35,6 +35,11 @@ __device__ __forceinline__ void load_chunk_x(const uint16_t* xr, int chunk, int 
             xv[w * HPW + pp] = __builtin_bit_cast(f16x2, a | b);
         }
     }
+}
+
+template <int BITS>
+__device__ __forceinline__ void load_chunk_x(const uint16_t* xr, int chunk, int act, f16x2* xv) {
+    load_chunk_pairs<BITS>(chunk, xv, [&](int i, uint32_t* out) { load8_f16(xr + i, act, out); });
 }
 
 // 3-bit codes come in chunks of 32 codes = 3 words (the row's bit string cut

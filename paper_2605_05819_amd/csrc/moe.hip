@@ -15,9 +15,13 @@
 //  * moe_prep_kernel: workgroup (linear, j, q), j < min(E, T*k), reads the
 //    routing table -- so no workgroup ever waits for another -- counts slots
 //    per expert, scans the counts and takes e = the j-th routed expert in
-//    ascending id order (none: it exits).  Each of its four waves computes
-//    t[slot][i] = A_e[i] . x_slot for one rank row i = 4q + wave of its
-//    linear over all of e's slots (four slots per pass).  Workgroup
+//    ascending id order (none: it exits).  It computes t[slot][i] =
+//    A_e[i] . x_slot for the rank rows i = 16q .. 16q + 15 of its linear over
+//    all of e's slots on MFMA, 16 slots per pass, its four waves splitting K.
+//    Bound by its chain (routing tables, then two rounds of loads): fewer,
+//    larger workgroups (one rank row per wave before) take 17.0 -> 12.9 us at
+//    512 slots over 128 experts of 2048 x 768, two linears of rank <= 32.  A
+//    gated call forms SiLU(g) u as it reads the activations.  Workgroup
 //    (0, j, 0) also writes entry j of the active-expert table and e's slots,
 //    in slot order, into the sorted slot list, and (linear, j, 0) that
 //    linear's rank of e; workgroups (linear, 0, 0) write the number of
@@ -82,6 +86,12 @@ constexpr int kStreamBlocks = 512;
 constexpr int kStreamDepth = 2;
 constexpr int kStreamMaxRows = (1 << 29) / kMaxSlots - 1;   // 31-bit byte offsets of fp32 outputs
 constexpr int kStreamMinExperts = 32, kStreamMinWidth = 36 << 10;
+// Gated calls off the one-launch path form SiLU(g) u in the preparation, once
+// per workgroup that reads the slot, up to this width (128 experts of 768: a
+// kernel of its own took 4.7 us of a layer); on wider rows the repeated
+// exponentials cost as much as that launch (16 experts of 1536: 10.8 against
+// 5.9 + 4.5 us).
+constexpr int kGateFuseMaxWidth = 1024;
 constexpr int kMoeTpw = 4;
 constexpr int kMoeNbuf = 1;
 
@@ -98,7 +108,7 @@ struct MoeLin {
     float* t;                // [T*k][r_max] (workspace)
     size_t q_stride, sz_stride, a_stride, b_stride;   // elements per expert
     int d_out, r_max;
-    int rq;                  // preparation workgroups per expert (4 rank rows each)
+    int rq;                  // preparation workgroups per expert (rr rank rows each)
     int bpe;                 // backbone batches per expert
     int prep_end;            // rank workgroups of linears 0 .. this one (prefix sum)
     int blk_end;             // backbone workgroups of linears 0 .. this one (prefix sum)
@@ -122,11 +132,12 @@ struct MoeArgs {
     f16x2* xp;               // [rows][d_in/2]
     float* sx;               // [rows][chunks]
     int ks, cps;             // K slices, chunks per slice
+    int rr;                  // rank rows per preparation workgroup: 16 or 4
     int rb;                  // direct path: rows per workgroup
     int nrbm;                // direct path: row blocks per (linear, slot) unit (the largest linear's)
 };
 
-template <int BITS>
+template <int BITS, bool GATED>
 __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
     constexpr int CPW = 32 / BITS, HPW = CPW / 2, PPC = 4 * HPW;
     // sids[S], mys[S] (this expert's slots, in slot order), hist[E] (slots
@@ -136,7 +147,7 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
     __shared__ int wsum[4][2];
     __shared__ int wcnt[4];
     __shared__ int sel, sel_lt, sel_n, srank;
-    __shared__ u32x4 xsh[4][256];          // a pass's activations, 4 slots x 2048 columns
+    __shared__ f32x4 tred[4][64];          // the waves' K parts of a 16 x 16 tile of t
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
@@ -149,8 +160,8 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
 
     if (blk < a.lin[a.n - 1].prep_end) {
         // workgroup (linear li, j, quad): the j-th routed expert (ascending
-        // id), its rank rows 4 quad .. 4 quad + 3 of linear li; every
-        // workgroup derives the routing itself
+        // id), its a.rr rank rows from a.rr quad of linear li; every workgroup
+        // derives the routing itself
         int li = 0;
         while (blk >= a.lin[li].prep_end) ++li;
         const MoeLin& L = a.lin[li];
@@ -290,60 +301,56 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
             }
             a.table[kTab * j + 4 + li] = rank;
         }
-        // t[slot][i] = A_e[i] . x_slot: wave w takes rank row i = 4 quad + w;
-        // each pass's activations (4 slots x 2048 columns) go into LDS once
-        // for the workgroup's four waves
-        const int i = 4 * quad + wave;
-        if (4 * quad >= rank) return;
-        const bool has = i < rank;
-        const uint16_t* ar = L.A + static_cast<size_t>(e) * L.a_stride + static_cast<size_t>(has ? i : 4 * quad) * a.d_in;
-        for (int j0 = 0; j0 < ne; j0 += 4) {
-            const uint16_t* xr[4];
-            int sl4[4];
+        // t[slot][i] = A_e[i] . x_slot for 16 slots and 16 rank rows at a
+        // time on v_mfma_f32_16x16x32_f16 (slots the A operand, rows of A_e
+        // the B operand, both in natural k order); the four waves split K,
+        // UN 32-column steps of loads in flight each.  Rows past the rank and
+        // absent slots repeat present ones and are not stored.
+        constexpr int UN = 8;
+        if (a.rr * quad >= rank) return;
+        const int g = lane >> 4, r = lane & 15;
+        const int i = a.rr * quad + r;
+        const uint16_t* ar = L.A + static_cast<size_t>(e) * L.a_stride +
+                             static_cast<size_t>(min(a.rr * quad + min(r, a.rr - 1), rank - 1)) * a.d_in + 8 * g;
+        const int nsteps = a.d_in / 32, spw = (nsteps + 3) / 4;
+        const int s0 = wave * spw, s1 = min(s0 + spw, nsteps);
+        for (int j0 = 0; j0 < ne; j0 += 16) {
+            const int sl = mys[min(j0 + r, ne - 1)];
+            const int xrow = a.x_per_slot ? sl : sl / a.k;
+            const uint16_t* xr = a.x + static_cast<size_t>(xrow) * a.d_in + 8 * g;
+            const uint16_t* ur = GATED ? a.u + static_cast<size_t>(xrow) * a.d_in + 8 * g : xr;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            for (int sb = s0; sb < s1; sb += UN) {
+                u32x4 av[UN], xv[UN], uv[GATED ? UN : 1];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                sl4[u] = mys[j0 + u < ne ? j0 + u : j0];
-                const int xrow = a.x_per_slot ? sl4[u] : sl4[u] / a.k;
-                xr[u] = a.x + static_cast<size_t>(xrow) * a.d_in;
-            }
-            float acc[4] = {0.f, 0.f, 0.f, 0.f};
-            for (int c0 = 0; c0 < a.d_in; c0 += 4 * 512) {
-                u32x4 av[4], xl[4];
-                const int cx = c0 + 8 * tid;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) xl[u] = *reinterpret_cast<const u32x4*>(xr[u] + (cx < a.d_in ? cx : 0));
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int c = c0 + 512 * q + 8 * lane;
-                    av[q] = *reinterpret_cast<const u32x4*>(ar + (c < a.d_in ? c : 0));
+                for (int v = 0; v < UN; ++v) {
+                    const int k = 32 * (sb + v < s1 ? sb + v : s0);
+                    av[v] = *reinterpret_cast<const u32x4*>(ar + k);
+                    xv[v] = *reinterpret_cast<const u32x4*>(xr + k);
+                    if constexpr (GATED) uv[v] = *reinterpret_cast<const u32x4*>(ur + k);
                 }
-                __syncthreads();                 // the previous pass's reads are done
+                __builtin_amdgcn_sched_barrier(0);   // all loads out before any is converted
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    xsh[u][tid] = cx < a.d_in ? act8_to_f16(xl[u], a.act) : u32x4{0u, 0u, 0u, 0u};
-                __syncthreads();
-                if (has) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const u32x4 xw = xsh[u][64 * q + lane];
-                            float d = 0.f;
-#pragma unroll
-                            for (int h = 0; h < 4; ++h) {
-                                const uint32_t ae = av[q][h], xe = xw[h];
-                                d = dot2(__builtin_bit_cast(f16x2, ae), __builtin_bit_cast(f16x2, xe), d);
-                            }
-                            acc[u] += d;
-                        }
+                for (int v = 0; v < UN; ++v) {
+                    if (sb + v < s1) {
+                        u32x4 x8;
+                        if constexpr (GATED) x8 = gated8_to_f16(xv[v], uv[v], a.act);
+                        else x8 = act8_to_f16(xv[v], a.act);
+                        acc = mfma(x8, av[v], acc);
                     }
                 }
             }
-            if (has) {
-                const float tot = wave_sum_multi<4>(acc);      // lane l: slot j0 + l / 16
-                const int u = lane >> 4;
-                if ((lane & 15) == 0 && j0 + u < ne) L.t[static_cast<size_t>(sl4[u]) * L.r_max + i] = tot;
+            tred[wave][lane] = acc;
+            __syncthreads();
+            // lane (g, r) of wave w: slot 4 g + w of the pass, rank row r
+            {
+                float tot = 0.f;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) tot += tred[v][lane][wave];
+                const int u = j0 + 4 * g + wave;
+                if (u < ne && r < a.rr && i < rank) L.t[static_cast<size_t>(mys[u]) * L.r_max + i] = tot;
             }
+            __syncthreads();                     // tred is reused by the next pass
         }
         return;
     }
@@ -355,7 +362,17 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
     const int row = static_cast<int>(item / chunks);
     const int c = static_cast<int>(item % chunks);
     f16x2 v[PPC];
-    load_chunk_x<BITS>(a.x + static_cast<size_t>(row) * a.d_in, c, a.act, v);
+    if constexpr (GATED) {
+        const uint16_t *gr = a.x + static_cast<size_t>(row) * a.d_in, *ur = a.u + static_cast<size_t>(row) * a.d_in;
+        load_chunk_pairs<BITS>(c, v, [&](int at, uint32_t out[4]) {
+            const u32x4 h = gated8_to_f16(*reinterpret_cast<const u32x4*>(gr + at),
+                                          *reinterpret_cast<const u32x4*>(ur + at), a.act);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { const uint32_t hq = h[q]; out[q] = hq; }
+        });
+    } else {
+        load_chunk_x<BITS>(a.x + static_cast<size_t>(row) * a.d_in, c, a.act, v);
+    }
     const f16x2 one = {static_cast<f16>(1.0f), static_cast<f16>(1.0f)};
     float sum = 0.f;
     f16x2* dst = a.xp + static_cast<size_t>(row) * (a.d_in / 2) + static_cast<size_t>(c) * PPC;
@@ -625,8 +642,7 @@ void moe_kernel(MoeArgs a) {
 // token with 8 routed experts this replaces the preparation launch and its
 // dependent memory round trips (ids, A_e rows, then the backbone's reads of
 // t and the activations).
-// The gated activations h = SiLU(g) u of every slot, 8 per thread, as fp16:
-// the input of the preparation and backbone kernels for a gated call.
+// The gated activations h = SiLU(g) u of every slot, 8 per thread, as fp16.
 __global__ __launch_bounds__(256) void moe_gate_kernel(const uint16_t* g, const uint16_t* u, uint16_t* h, size_t n8,
                                                        int act) {
     const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -1708,6 +1724,15 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
     const int nkb = (d_in + 127) / 128;
     const bool stream = bits == 4 && nkb <= 32 && w[0].G % 64 == 0 && max_active >= kStreamMinExperts &&
                         max_active * d_in >= kStreamMinWidth;
+    // Rank rows per preparation workgroup: 16 where that gives most CUs one,
+    // fewer where it would leave them idle (a workgroup streams its rows of
+    // A_e at one CU's share of the memory rate): 16 experts, 2048 x 768, rank 32:
+    // a layer 39.8 us with 16 rows, 38.7 with 4; 128 experts, 64 slots: 64.3 with
+    // 16, 67.1 with 4.  Gated calls repeat SiLU(g) u per workgroup, so they go
+    // to fewer rows later.
+    int wide = 0;
+    for (int i = 0; i < n; ++i) wide += max_active * ((r_max[i] + 15) / 16);
+    a.rr = a.u && d_in <= kGateFuseMaxWidth ? (wide > 32 ? 16 : 4) : (wide >= 192 ? 16 : wide >= 96 && d_in <= 2048 ? 8 : 4);
     int prep_end = 0, blk_end = 0;
     for (int i = 0; i < n; ++i) {
         MoeLin& L = a.lin[i];
@@ -1721,7 +1746,7 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
         L.b_stride = static_cast<size_t>(w[i].d_out) * r_max[i];
         L.d_out = w[i].d_out;
         L.r_max = r_max[i];
-        L.rq = r_max[i] > 0 ? (r_max[i] + 3) / 4 : 1;
+        L.rq = r_max[i] > 0 ? (r_max[i] + a.rr - 1) / a.rr : 1;
         const int rgroups = (w[i].d_out + rows_per_wave(bits) - 1) / rows_per_wave(bits);
         L.bpe = stream ? (w[i].d_out + 15) / 16
                        : on_mfma ? (w[i].d_out + 16 * kMoeTpw - 1) / (16 * kMoeTpw)
@@ -1753,11 +1778,7 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
     const int nb = rmax == 0 ? 0 : (rmax <= per ? 1 : (rmax <= 2 * per ? 2 : 4));
     if (rmax > 4 * per) return hipErrorInvalidConfiguration;
 
-    if (a.u) {
-        // gated input off the one-launch path: SiLU(g) u once for every slot
-        // (each preparation workgroup forming it for its slots had repeated
-        // the exponentials once per rank row: 52 against 11 us at 512 slots),
-        // then the plain path on it
+    if (a.u && d_in > kGateFuseMaxWidth) {
         uint16_t* h = reinterpret_cast<uint16_t*>(wsb + l.h);
         const size_t n8 = static_cast<size_t>(S) * d_in / 8;
         hipLaunchKernelGGL(moe_gate_kernel, dim3(static_cast<unsigned>((n8 + 255) / 256)), dim3(256), 0, st, a.x, a.u,
@@ -1772,10 +1793,9 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
     const long long items = static_cast<long long>(rows) * chunks;
     const unsigned pgrid = static_cast<unsigned>(prep_end + (items + 255) / 256);
     const size_t plds = static_cast<size_t>(2 * S + 2 * E) * sizeof(int);
-    if (bits == 4)
-        hipLaunchKernelGGL(moe_prep_kernel<4>, dim3(pgrid), dim3(256), plds, st, a);
-    else
-        hipLaunchKernelGGL(moe_prep_kernel<2>, dim3(pgrid), dim3(256), plds, st, a);
+    auto prep = bits == 4 ? (a.u ? moe_prep_kernel<4, true> : moe_prep_kernel<4, false>)
+                          : (a.u ? moe_prep_kernel<2, true> : moe_prep_kernel<2, false>);
+    hipLaunchKernelGGL(prep, dim3(pgrid), dim3(256), plds, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (stream) {

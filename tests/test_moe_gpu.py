@@ -604,3 +604,30 @@ def test_streamed_experts_keep_large_and_small_factor_products():
     assert np.abs(xv[0] @ A[ids[0, 0]].astype(np.float64).T).max() > 65504
     for t in range(T):
         assert rel_l2(got[t], ref[t]) <= 2.0 ** -22 + 2.0 ** -24 * np.sqrt(d_in)
+
+
+@pytest.mark.parametrize("bits,d_in,E,T,k,r_max,act", [
+    (4, 768, 40, 24, 4, 33, torch.bfloat16),     # fused, 16 rank rows a workgroup, partial last
+    (4, 1024, 6, 9, 3, 21, torch.float16),       # fused, 4 rank rows a workgroup
+    (4, 1152, 8, 16, 2, 40, torch.float16),      # past the fused width: the gate kernel
+    (2, 512, 20, 20, 3, 16, torch.bfloat16),     # 2-bit, fused
+])
+def test_gated_down_preparation(bits, d_in, E, T, k, r_max, act):
+    """The gated call's preparation on each side of its rules: fused and as a
+    kernel of its own, 4 and 16 rank rows per workgroup, more than 16 slots on
+    an expert."""
+    d_out, G = 70, 128 if bits == 4 else 64
+    Q, s, z, A, B = _oracle_experts(E, d_out, d_in, bits, G, r_max, 80 + d_in, svd=False)
+    ranks = wl.moe_expert_ranks(81, 0, 0, E, levels=(0, r_max // 2, r_max))
+    ids, _ = wl.routing(T, 82, 0, E, k)
+    ids = ids.copy()
+    ids[:, 0] = np.where(np.arange(T) < T * 4 // 5, 1, ids[:, 0])
+    dt = "fp16" if act == torch.float16 else "bf16"
+    g, u = (wl.activation((T, k, d_in), 83, 0, i, dtype=dt) for i in range(2))
+    h = (g.values / (1.0 + np.exp(-g.values)) * u.values).astype(np.float16).astype(np.float64)
+    ex = _device_experts(Q, s, z, A, B, ranks, d_out, d_in, bits, G, r_max)
+    y = cl.moe_linear_decode_gated(ex, dev_u16(g.bits, act), dev_u16(u.bits, act), torch.from_numpy(ids).cuda(),
+                                   out_dtype=torch.float32)
+    ref = _full_ref(Q, s, z, A, B, ranks, h, ids, True, bits, G, d_in)
+    # the fp16 rounding of h falls on the other side of a tie here and there
+    assert rel_l2(out_to_numpy(y), ref) <= 2.0 ** -12
