@@ -16,7 +16,7 @@
 // Steps (all fp64, one stream, the host waits once):
 //  1. E = W - s (q - z) elementwise.
 //  2. The Gram matrix over the smaller side, C = E^T E (d_in <= d_out) or
-//     C = E E^T, with a tiled fp64 GEMM (64 x 64 tiles through LDS).
+//     C = E E^T, with a tiled fp64 MFMA GEMM (64 x 64 tiles through LDS).
 //  3. Eigen-decomposition C = X diag(lambda) X^T, X for the leading r_max only:
 //     Householder reduction to tridiagonal T = Q^T C Q, one launch per
 //     reflector; every eigenvalue of T by bisection on Sturm counts, 64
@@ -103,60 +103,81 @@ __global__ __launch_bounds__(256) void residual_kernel(const float* __restrict__
     E[idx] = static_cast<double>(W[idx]) - what;
 }
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 // out[i * ldo + j] = sum_k X[i * xi + k * xk] * Y[j * yj + k * yk]  (fp64)
-// 64 x 64 output tile per 256-thread workgroup, 4 x 4 per thread, k in steps
-// of 16 through LDS.  XK1 / YK1: the operand is contiguous along k (else along
-// i / j), which decides the load order so that loads coalesce.
+// 64 x 64 output tile per 256-thread workgroup, each wave a 32 x 32 quadrant
+// of it on v_mfma_f64_16x16x4_f64; k in steps of 16 through two LDS buffers,
+// the next step's loads in flight during this one's products (a lone
+// workgroup per CU has nothing else to hide them).  XK1 / YK1: the operand is
+// contiguous along k (else along i / j), which decides the load order so that
+// loads coalesce.  Bound by the matrix cores' fp64 rate and, at 16 x 16 tiles,
+// by one workgroup's chain of k steps: 1024 x 1024 x 4096 245 us (fp64 FMAs on the
+// VALU, 4 x 4 outputs a thread: 748).
 template <bool XK1, bool YK1>
 __global__ __launch_bounds__(256) void gemm_nt_f64(const double* __restrict__ X, size_t xi, size_t xk,
                                                    const double* __restrict__ Y, size_t yj, size_t yk, int I, int J,
                                                    int K, double* __restrict__ out, size_t ldo) {
     constexpr int BT = 64, BK = 16;
-    __shared__ double xs[BK][BT + 1];
-    __shared__ double ys[BK][BT + 1];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
+    __shared__ double xs[2][BK][BT + 1];
+    __shared__ double ys[2][BK][BT + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g = lane >> 4, r = lane & 15;
     const int i0 = blockIdx.y * BT, j0 = blockIdx.x * BT;
-    double acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += BK) {
+    const int wi = 32 * (wave >> 1), wj = 32 * (wave & 1);
+    // element l of this thread: row (of the tile) and k of the step
+    auto row_of = [&](bool k1, int l) { const int e = tid + 256 * l; return k1 ? e / BK : e & (BT - 1); };
+    auto k_of = [&](bool k1, int l) { const int e = tid + 256 * l; return k1 ? e & (BK - 1) : e / BT; };
+    double xr[4], yr[4];
+    auto load = [&](int k0) {
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
-            const int e = tid + 256 * l;
-            int ii, kk;
-            if (XK1) { kk = e & (BK - 1); ii = e / BK; } else { ii = e & (BT - 1); kk = e / BT; }
-            const int gi = i0 + ii, gk = k0 + kk;
-            xs[kk][ii] = (gi < I && gk < K) ? X[gi * xi + gk * xk] : 0.0;
-            int jj, kj;
-            if (YK1) { kj = e & (BK - 1); jj = e / BK; } else { jj = e & (BT - 1); kj = e / BT; }
-            const int gj = j0 + jj, gkj = k0 + kj;
-            ys[kj][jj] = (gj < J && gkj < K) ? Y[gj * yj + gkj * yk] : 0.0;
+            const int gi = i0 + row_of(XK1, l), gk = k0 + k_of(XK1, l);
+            xr[l] = (gi < I && gk < K) ? X[gi * xi + gk * xk] : 0.0;
+            const int gj = j0 + row_of(YK1, l), gkj = k0 + k_of(YK1, l);
+            yr[l] = (gj < J && gkj < K) ? Y[gj * yj + gkj * yk] : 0.0;
         }
-        __syncthreads();
+    };
+    auto store = [&](int st) {
 #pragma unroll
-        for (int kk = 0; kk < BK; ++kk) {
-            double a[4], b[4];
+        for (int l = 0; l < 4; ++l) {
+            xs[st][k_of(XK1, l)][row_of(XK1, l)] = xr[l];
+            ys[st][k_of(YK1, l)][row_of(YK1, l)] = yr[l];
+        }
+    };
+    f64x4 acc[2][2] = {};
+    load(0);
+    store(0);
+    __syncthreads();
+    for (int k0 = 0, st = 0; k0 < K; k0 += BK, st ^= 1) {
+        if (k0 + BK < K) load(k0 + BK);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                a[u] = xs[kk][ty + 16 * u];
-                b[u] = ys[kk][tx + 16 * u];
+        for (int kk = 0; kk < BK; kk += 4) {
+            double a[2], b[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                a[u] = xs[st][kk + g][wi + 16 * u + r];
+                b[u] = ys[st][kk + g][wj + 16 * u + r];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
+                for (int v = 0; v < 2; ++v)
+                    acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
         }
+        if (k0 + BK < K) store(st ^ 1);
         __syncthreads();
     }
+    // lane (g, r) holds rows 4 e + g of column r of a 16 x 16 tile
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int gi = i0 + ty + 16 * u;
-        if (gi >= I) continue;
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int gj = j0 + tx + 16 * v;
-            if (gj < J) out[gi * ldo + gj] = acc[u][v];
-        }
-    }
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int gi = i0 + wi + 16 * u + 4 * e + g, gj = j0 + wj + 16 * v + r;
+                if (gi < I && gj < J) out[gi * ldo + gj] = acc[u][v][e];
+            }
 }
 
 // Sum over the 256 threads of a workgroup, in a fixed order; red: 4 doubles
@@ -192,7 +213,7 @@ __device__ __forceinline__ double recip_f64(double q) {
 // rows' loads are issued before the reductions.  Row i always belongs to
 // workgroup i mod grid.  Bound by the chain of one launch (two reductions; 4.4
 // us a step at <= 256 columns, 7.2 at 1024) up to n ~ 2000, beyond by the 16
-// n^2 bytes.  The whole call at 1024 x 4096, r_max 128: 134 -> 8.6 ms, 4096 x
+// n^2 bytes.  The whole call at 1024 x 4096, r_max 128: 134 -> 8.0 ms, 4096 x
 // 4096: 4.9 -> 0.13 s, against cyclic Jacobi (10 to 18 sweeps of n - 1 rounds
 // of two launches over C and X).
 template <int CPT, int R>
