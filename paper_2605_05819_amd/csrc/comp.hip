@@ -212,9 +212,9 @@ __device__ __forceinline__ double recip_f64(double q) {
 // and the new v stay in its registers) and R rows at a time; the first R
 // rows' loads are issued before the reductions.  Row i always belongs to
 // workgroup i mod grid.  Bound by the chain of one launch (two reductions; 4.4
-// us a step at <= 256 columns, 7.2 at 1024) up to n ~ 2000, beyond by the 16
-// n^2 bytes.  The whole call at 1024 x 4096, r_max 128: 134 -> 8.0 ms, 4096 x
-// 4096: 4.9 -> 0.13 s, against cyclic Jacobi (10 to 18 sweeps of n - 1 rounds
+// us a step at <= 256 columns, 6.3 at 1024) up to n ~ 2000, beyond by the 16
+// n^2 bytes.  The whole call at 1024 x 4096, r_max 128: 134 -> 7.4 ms, 4096 x
+// 4096: 4.9 -> 0.11 s, against cyclic Jacobi (10 to 18 sweeps of n - 1 rounds
 // of two launches over C and X).
 template <int CPT, int R>
 __global__ __launch_bounds__(256) void householder_step_kernel(double* __restrict__ C, int n, int k,
@@ -659,8 +659,11 @@ hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uin
 
     for (int k = 0; k < n; ++k) {
         by_columns(n - (k & ~63), [&](auto cpt) {
-            constexpr int CPT = decltype(cpt)::value, R = CPT > 8 ? 2 : 4;
-            hipLaunchKernelGGL((householder_step_kernel<CPT, R>), dim3(n < 256 ? n : 256), dim3(256), 0, st, C, n, k, V,
+            // rows in hand per workgroup, and workgroups: two per CU where the
+            // trailing matrix has the rows (1024 x 4096 7.97 -> 7.37 ms, 4096 x
+            // 4096 128 -> 105 ms against 256 workgroups of 4 rows in hand)
+            constexpr int CPT = decltype(cpt)::value, R = CPT <= 2 ? 1 : 2, G = CPT == 1 ? 256 : 512;
+            hipLaunchKernelGGL((householder_step_kernel<CPT, R>), dim3(n < G ? n : G), dim3(256), 0, st, C, n, k, V,
                                p[k & 1], p[(k & 1) ^ 1], tau, d, e);
         });
     }
