@@ -209,6 +209,20 @@ __device__ __forceinline__ void split_f16x2(float a, float b, uint32_t& hi, uint
     lo = __builtin_bit_cast(uint32_t, f16x2{la, lb});
 }
 
+// Two fp32 values, |v| < 2, as three fp16 parts: v = hi + 2^-11 mid + 2^-22 lo,
+// exactly down to 2^-23 and to 2^-47 absolute below (each remainder is exact
+// in fp32, and its factor of 2^11 keeps the next part above fp16's subnormals).
+__device__ __forceinline__ void split3_f16x2(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    const f16 ha = static_cast<f16>(a), hb = static_cast<f16>(b);
+    const float ra = (a - static_cast<float>(ha)) * 0x1p11f, rb = (b - static_cast<float>(hb)) * 0x1p11f;
+    const f16 ma = static_cast<f16>(ra), mb = static_cast<f16>(rb);
+    const f16 la = static_cast<f16>((ra - static_cast<float>(ma)) * 0x1p11f);
+    const f16 lb = static_cast<f16>((rb - static_cast<float>(mb)) * 0x1p11f);
+    hi = __builtin_bit_cast(uint32_t, f16x2{ha, hb});
+    mid = __builtin_bit_cast(uint32_t, f16x2{ma, mb});
+    lo = __builtin_bit_cast(uint32_t, f16x2{la, lb});
+}
+
 // acc += s * p, elementwise in fp32
 __device__ __forceinline__ f32x4 fma4(float s, const f32x4& p, const f32x4& acc) {
     f32x4 r;

@@ -304,8 +304,11 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
         // t[slot][i] = A_e[i] . x_slot for 16 slots and 16 rank rows at a
         // time on v_mfma_f32_16x16x32_f16 (slots the A operand, rows of A_e
         // the B operand, both in natural k order); the four waves split K,
-        // UN 32-column steps of loads in flight each.  Rows past the rank and
-        // absent slots repeat present ones and are not stored.
+        // UN 32-column steps of loads in flight each.  Four accumulators: the
+        // shorter chains leave t's error at the level of pairwise fp32 sums
+        // (where the factor term dominates the output, 1.2e-7 of it against
+        // 1.6e-7 with one).  Rows past the rank and absent slots repeat
+        // present ones and are not stored.
         constexpr int UN = 8;
         if (a.rr * quad >= rank) return;
         const int g = lane >> 4, r = lane & 15;
@@ -319,7 +322,7 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
             const int xrow = a.x_per_slot ? sl : sl / a.k;
             const uint16_t* xr = a.x + static_cast<size_t>(xrow) * a.d_in + 8 * g;
             const uint16_t* ur = GATED ? a.u + static_cast<size_t>(xrow) * a.d_in + 8 * g : xr;
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            f32x4 acc[4] = {};
             for (int sb = s0; sb < s1; sb += UN) {
                 u32x4 av[UN], xv[UN], uv[GATED ? UN : 1];
 #pragma unroll
@@ -330,17 +333,20 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
                     if constexpr (GATED) uv[v] = *reinterpret_cast<const u32x4*>(ur + k);
                 }
                 __builtin_amdgcn_sched_barrier(0);   // all loads out before any is converted
+                if (!GATED && a.act != DT_FP16) {
+#pragma unroll
+                    for (int v = 0; v < UN; ++v) xv[v] = act8_to_f16(xv[v], a.act);
+                }
 #pragma unroll
                 for (int v = 0; v < UN; ++v) {
                     if (sb + v < s1) {
-                        u32x4 x8;
+                        u32x4 x8 = xv[v];
                         if constexpr (GATED) x8 = gated8_to_f16(xv[v], uv[v], a.act);
-                        else x8 = act8_to_f16(xv[v], a.act);
-                        acc = mfma(x8, av[v], acc);
+                        acc[v & 3] = mfma(x8, av[v], acc[v & 3]);
                     }
                 }
             }
-            tred[wave][lane] = acc;
+            tred[wave][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
             __syncthreads();
             // lane (g, r) of wave w: slot 4 g + w of the pass, rank row r
             {
@@ -935,12 +941,12 @@ __device__ __forceinline__ void buffer_store_out(void* y, uint32_t n, int idx, f
 // factor row only.  Absent slots of a pass repeat a present one; their rows of
 // the product are not stored.  Codes become the exact integers q - z, each
 // quantization group's partial is scaled in fp32, the rank term is MFMA steps
-// over [t | B_e] with t as fp16 hi and lo parts of t 2^-e (e the exponent of
-// the step's largest |t| of the slot, restored in fp32: neither overflow nor
-// fp16's subnormal range is met); the K parts meet in LDS in a fixed order;
+// over [t | B_e] with t 2^-e as three fp16 parts that hold all of its 24 bits
+// (e the exponent of the step's largest |t| of the slot, restored in fp32:
+// neither overflow nor fp16's subnormal range is met); the K parts meet in LDS in a fixed order;
 // one rounding.  Two tiles in flight (four layers of 128 experts, 2048 x 768, at
 // 512 slots: 502 us; three 510, one 527) and two workgroups per CU (one: 1.6
-// times the time; 233 registers do not fit three).
+// times the time; 256 registers do not fit three).
 // Where the line lies: NBK <= 4 blocks on KW <= 8 waves keep the activations
 // within 64 registers; groups of 32 codes (four scales per block) were 2 %
 // slower than on the kernels below, and so were few experts or short rows,
@@ -1100,7 +1106,7 @@ __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves
     // t operand of the rank step at factor column kr, and the factors that
     // restore it for this lane's accumulators (slots 4 g .. 4 g + 3)
     struct TOp {
-        u32x4 hi, lo;
+        u32x4 hi, mid, lo;
         f32x4 up;
     };
     auto t_operand = [&](const MoeLin& L, int rank, int kr) {
@@ -1111,23 +1117,24 @@ __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves
         }
         const float* trow = L.t + static_cast<size_t>(sl) * L.r_max;
         const int k = kr + 8 * g;
-        float v[8], m = 0.f;
+        float v[8], top = 0.f;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const float tv = trow[k + q < L.r_max ? k + q : 0];
             v[q] = k + q < rs ? tv : 0.f;
-            m = fmaxf(m, fabsf(v[q]));
+            top = fmaxf(top, fabsf(v[q]));
         }
-        m = fmaxf(m, __shfl_xor(m, 16, 64));
-        m = fmaxf(m, __shfl_xor(m, 32, 64));
-        const uint32_t ex = min(max(__builtin_bit_cast(uint32_t, m) >> 23, 1u), 253u);
+        top = fmaxf(top, __shfl_xor(top, 16, 64));
+        top = fmaxf(top, __shfl_xor(top, 32, 64));
+        const uint32_t ex = min(max(__builtin_bit_cast(uint32_t, top) >> 23, 1u), 253u);
         const float down = __builtin_bit_cast(float, (254u - ex) << 23);
         const float up = __builtin_bit_cast(float, ex << 23);
         TOp o;
-        uint32_t h[4], l[4];
+        uint32_t h[4], m[4], l[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) split_f16x2(v[2 * q] * down, v[2 * q + 1] * down, h[q], l[q]);
+        for (int q = 0; q < 4; ++q) split3_f16x2(v[2 * q] * down, v[2 * q + 1] * down, h[q], m[q], l[q]);
         o.hi = u32x4{h[0], h[1], h[2], h[3]};
+        o.mid = u32x4{m[0], m[1], m[2], m[3]};
         o.lo = u32x4{l[0], l[1], l[2], l[3]};
 #pragma unroll
         for (int q = 0; q < 4; ++q) o.up[q] = __shfl(up, 4 * g + q, 64);
@@ -1143,9 +1150,10 @@ __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves
             const uint32_t hi = k + 2 * q + 1 < rank ? v & 0xffff0000u : 0u;
             bw[q] = lo | hi;
         }
-        const f32x4 pp = mfma(o.lo, bw, mfma(o.hi, bw, fzero));
+        const f32x4 ph = mfma(o.hi, bw, fzero), pm = mfma(o.mid, bw, fzero), pl = mfma(o.lo, bw, fzero);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] = fmaf(o.up[q], pp[q], acc[q]);
+        for (int q = 0; q < 4; ++q)
+            acc[q] = fmaf(o.up[q], fmaf(0x1p-11f, fmaf(0x1p-11f, pl[q], pm[q]), ph[q]), acc[q]);
     };
 
     Pos lp, cp;
@@ -1166,7 +1174,7 @@ __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves
         if (!over(lp) && advance(lp) && !over(lp)) load_segment(lp);
     }
     int rank = rank_of(cp.ae, cp.li);
-    TOp t0{zero, zero, fzero};
+    TOp t0{zero, zero, zero, fzero};
     if (32 * kw < rank) t0 = t_operand(a.lin[cp.li], rank, 32 * kw);
     int par = 0;
     // Past the end of the list a step only keeps the pipeline's shape: a way

@@ -606,6 +606,27 @@ def test_streamed_experts_keep_large_and_small_factor_products():
         assert rel_l2(got[t], ref[t]) <= 2.0 ** -22 + 2.0 ** -24 * np.sqrt(d_in)
 
 
+@pytest.mark.parametrize("T,k,E", [(8, 8, 64), (64, 8, 40)])
+def test_streamed_experts_keep_factor_products_next_to_a_large_one(T, k, E):
+    """A slot's t = A x with one factor column 2^14 times the others whose B
+    column is zero, on a backbone of scale zero: the result is the small
+    columns' alone, so a t rounded relative to the largest one shows.  Bound:
+    fp32 sums of d_in products and of r_max factor terms."""
+    d_in, d_out, r_max = 2048, 64, 24
+    Q, s, z, A, B = _oracle_experts(E, d_out, d_in, 4, 128, r_max, 73, svd=False)
+    A, B, s = A.copy(), B.copy(), np.zeros_like(s)
+    A[:, 5] = (A[:, 5].astype(np.float64) * 2.0 ** 14).astype(np.float16)
+    assert np.isfinite(A.astype(np.float64)).all()
+    B[:, :, 5] = 0
+    ids, _ = wl.routing(T, 74, 0, E, k)
+    x = wl.activation((T, d_in), 75, 0, 1)
+    ranks = np.full(E, r_max, np.int32)
+    ex = _device_experts(Q, s, z, A, B, ranks, d_out, d_in, 4, 128, r_max)
+    got = _run(ex, x.bits, torch.float16, ids, torch.float32, False)
+    ref = _full_ref(Q, s, z, A, B, ranks, x.values, ids, False, 4, 128, d_in)
+    assert rel_l2(got, ref) <= 2.0 ** -22 + 2.0 ** -24 * np.sqrt(d_in)
+
+
 @pytest.mark.parametrize("bits,d_in,E,T,k,r_max,act", [
     (4, 768, 40, 24, 4, 33, torch.bfloat16),     # fused, 16 rank rows a workgroup, partial last
     (4, 1024, 6, 9, 3, 21, torch.float16),       # fused, 4 rank rows a workgroup
