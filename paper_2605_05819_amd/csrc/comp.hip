@@ -19,10 +19,12 @@
 //     C = E E^T, with a tiled fp64 MFMA GEMM (64 x 64 tiles through LDS).
 //  3. Eigen-decomposition C = X diag(lambda) X^T, X for the leading r_max only:
 //     Householder reduction to tridiagonal T = Q^T C Q, one launch per
-//     reflector; every eigenvalue of T by bisection on Sturm counts, 64
-//     points of an interval per wave and round; eigenvectors of T by inverse
-//     iteration, one lane per vector, with the vectors of close eigenvalues
-//     orthogonalised among each other; X = Q Z.
+//     reflector; T split into blocks where a coupling is within the
+//     reduction's rounding; every eigenvalue of each block by bisection on
+//     Sturm counts, 64 points of an interval per wave and round; eigenvectors
+//     of the blocks by inverse iteration, one lane per vector, with the
+//     vectors of a block's close eigenvalues orthogonalised among each other;
+//     X = Q Z.
 //  4. sigma = sqrt(lambda), descending.  If X holds right vectors V:
 //     A = sqrt(sigma) V^T and
 //     B = E V / sqrt(sigma) (= U sqrt(sigma)); if it holds left vectors U:
@@ -47,15 +49,25 @@ namespace {
 constexpr int kInverseSweeps = 2;
 // Bisection rounds: 65-section of an interval of width 2 |T| down to 2^-53 |T|.
 constexpr int kSections = 9;
-// Eigenvalues closer than this (relative to |T|) have their vectors
+// Eigenvalues of a block closer than this (relative to |T|) have their vectors
 // orthogonalised; beyond it inverse iteration alone leaves them orthogonal to
 // better than 1e-9, far below the rounding of the fp16 factors.
 constexpr double kCluster = 1e-6;
+// A coupling e_i is dropped, and T falls into two blocks there, where it is
+// within kDrop sqrt(n) (|d_i| + |d_i+1|): the rounding of the n reflectors
+// before it.  Left in, it does not separate the two sides and inverse iteration
+// divides by it.
+constexpr double kDrop = 4.5e-16;
+// Shifts of one block's eigenvalues are kept this far apart (relative to |T|),
+// about two roundings of an eigenvalue: with equal shifts every vector of a
+// cluster turns into the one nearest the shift (the same is done in Jessup and
+// Ipsen's analysis of inverse iteration and in LAPACK's xSTEIN).
+constexpr double kShift = 4e-16;
 
 size_t up256(size_t n) { return (n + 255) / 256 * 256; }
 
 struct CompLayout {
-    size_t E, C, V, tau, lam, d, e, de, p, bounds, scale, sign, Xr, P, total;
+    size_t E, C, V, tau, lam, row_lam, d, e, de, p, blk, order, rank_of, bounds, scale, sign, Xr, P, total;
 };
 
 CompLayout comp_layout(int d_out, int d_in, int r_max) {
@@ -67,11 +79,15 @@ CompLayout comp_layout(int d_out, int d_in, int r_max) {
     l.V = l.C + up256(n * n * 8);
     l.tau = l.V + up256(n * n * 8);
     l.lam = l.tau + up256(n * 8);
-    l.d = l.lam + up256(n * 8);
+    l.row_lam = l.lam + up256(n * 8);
+    l.d = l.row_lam + up256(n * 8);
     l.e = l.d + up256(n * 8);
     l.de = l.e + up256(n * 8);
     l.p = l.de + up256(n * 16);
-    l.bounds = l.p + up256(n * 16);
+    l.blk = l.p + up256(n * 16);
+    l.order = l.blk + up256(n * 8);
+    l.rank_of = l.order + up256(n * 4);
+    l.bounds = l.rank_of + up256(n * 4);
     l.scale = l.bounds + 256;
     l.sign = l.scale + up256(static_cast<size_t>(r_max) * 8 + 8);
     l.Xr = l.sign + up256(static_cast<size_t>(r_max) * 8 + 8);
@@ -277,7 +293,9 @@ __global__ __launch_bounds__(256) void householder_step_kernel(double* __restric
     q = block_sum_f64(q, red[1]);
     const double x0 = next;
     double t = 0.0, beta = x0, inv = 0.0;
-    if (q != 0.0) {
+    // a tail whose squares fall out of the normal range (E is fp32, so it is
+    // below 1e-55 of |T|) is left, for t would not fit v any more
+    if (q > 1e-290) {
         const double norm = sqrt(fma(x0, x0, q));
         beta = x0 >= 0.0 ? -norm : norm;
         t = (beta - x0) / beta;
@@ -324,50 +342,83 @@ __global__ __launch_bounds__(256) void householder_step_kernel(double* __restric
     }
 }
 
-// (d_i, e_i-1^2) pairs for the Sturm counts; bounds = {lower and upper end of
-// the Gershgorin discs, |T|, smallest pivot}.  One workgroup.
-__global__ __launch_bounds__(256) void tridiagonal_prep_kernel(const double* __restrict__ d,
-                                                               const double* __restrict__ e, int n,
-                                                               double2* __restrict__ de, double* __restrict__ bounds) {
+// The couplings within the rounding dropped (e set to zero); blk[i] = the rows
+// of i's block; (d_i, e_i-1^2) pairs for the Sturm counts; bounds = {lower and
+// upper end of the Gershgorin discs, |T|, smallest pivot, 1 if T is not
+// finite}.  One workgroup, a run of rows per thread.
+__global__ __launch_bounds__(256) void tridiagonal_prep_kernel(const double* __restrict__ d, double* __restrict__ e,
+                                                               int n, double2* __restrict__ de,
+                                                               int2* __restrict__ blk, double* __restrict__ bounds) {
     __shared__ double lo[256], hi[256], em[256];
+    __shared__ int first[256], last[256], odd[256];
+    const int tid = threadIdx.x, per = (n + 255) / 256;
+    const int i0 = min(tid * per, n), i1 = min(i0 + per, n);
+    const double tol = kDrop * sqrt(static_cast<double>(n));
+    for (int i = i0; i < i1; ++i)
+        if (i + 1 < n && fabs(e[i]) <= tol * (fabs(d[i]) + fabs(d[i + 1]))) e[i] = 0.0;
+    __syncthreads();
+    auto starts = [&](int i) { return i == 0 || e[i - 1] == 0.0; };
     double l = 1e308, h = -1e308, m = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) {
+    int f = n, t = -1, bad = 0;
+    for (int i = i0; i < i1; ++i) {
         const double el = i > 0 ? e[i - 1] : 0.0, er = i + 1 < n ? e[i] : 0.0;
         const double di = d[i], rad = fabs(el) + fabs(er);
+        bad |= !(fabs(di) + rad < 1e300);
         de[i] = make_double2(di, el * el);
         l = fmin(l, di - rad);
         h = fmax(h, di + rad);
         m = fmax(m, el * el);
+        if (starts(i)) {
+            f = min(f, i);
+            t = i;
+        }
     }
-    lo[threadIdx.x] = l; hi[threadIdx.x] = h; em[threadIdx.x] = m;
+    lo[tid] = l; hi[tid] = h; em[tid] = m;
+    first[tid] = f; last[tid] = t; odd[tid] = bad;
+    __syncthreads();
+    int beg = 0, end = n;
+    for (int u = 0; u < tid; ++u) beg = max(beg, last[u]);
+    for (int u = tid + 1; u < 256; ++u) end = min(end, first[u]);
+    for (int i = i0; i < i1; ++i) {
+        if (starts(i)) beg = i;
+        blk[i].x = beg;
+    }
+    for (int i = i1 - 1; i >= i0; --i) {
+        blk[i].y = end;
+        if (starts(i)) end = i;
+    }
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            lo[threadIdx.x] = fmin(lo[threadIdx.x], lo[threadIdx.x + s]);
-            hi[threadIdx.x] = fmax(hi[threadIdx.x], hi[threadIdx.x + s]);
-            em[threadIdx.x] = fmax(em[threadIdx.x], em[threadIdx.x + s]);
+        if (tid < s) {
+            lo[tid] = fmin(lo[tid], lo[tid + s]);
+            hi[tid] = fmax(hi[tid], hi[tid + s]);
+            em[tid] = fmax(em[tid], em[tid + s]);
+            odd[tid] |= odd[tid + s];
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         const double norm = fmax(fabs(lo[0]), fabs(hi[0]));
         const double pad = 4e-16 * norm * sqrt(static_cast<double>(n));
         bounds[0] = lo[0] - pad;
         bounds[1] = hi[0] + pad;
         bounds[2] = norm;
         bounds[3] = 2.3e-308 * fmax(1.0, em[0]);
+        bounds[4] = odd[0];
     }
 }
 
-// Eigenvalue j (descending), one wave each: the number of eigenvalues below x
-// is the number of negative pivots of T - x; each round every lane counts at
-// one of 64 points of the interval.
-__global__ __launch_bounds__(256) void bisect_kernel(const double2* __restrict__ de, int n,
-                                                     const double* __restrict__ bounds, double* __restrict__ lam,
-                                                     float* __restrict__ sigma) {
+// row_lam[j] for row j of a block: the block's (j - first row)-th largest
+// eigenvalue, one wave each: the number of eigenvalues below x is the number
+// of negative pivots of T - x; each round every lane counts at one of 64
+// points of the interval.
+__global__ __launch_bounds__(256) void bisect_kernel(const double2* __restrict__ de, const int2* __restrict__ blk,
+                                                     int n, const double* __restrict__ bounds,
+                                                     double* __restrict__ row_lam) {
     const int j = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
     if (j >= n) return;
-    const int lane = threadIdx.x & 63, below = n - 1 - j;
+    const int beg = blk[j].x, end = blk[j].y;
+    const int lane = threadIdx.x & 63, below = end - 1 - j;
     double lo = bounds[0], hi = bounds[1];
     const double pivmin = bounds[3];
     for (int round = 0; round < kSections; ++round) {
@@ -376,7 +427,7 @@ __global__ __launch_bounds__(256) void bisect_kernel(const double2* __restrict__
         int count = 0;
         double q = 1.0;
 #pragma unroll 8
-        for (int i = 0; i < n; ++i) {
+        for (int i = beg; i < end; ++i) {
             const double2 t = de[i];
             q = fma(-t.y, recip_f64(q), t.x - x);
             if (fabs(q) < pivmin) q = -pivmin;
@@ -388,46 +439,81 @@ __global__ __launch_bounds__(256) void bisect_kernel(const double2* __restrict__
         if (first < 64) hi = fma(width, first + 1.0, base);
         if (first > 0) lo = fma(width, static_cast<double>(first), base);
     }
-    if (lane == 0) {
-        const double l = bounds[2] == 0.0 ? 0.0 : 0.5 * (lo + hi);
-        lam[j] = l;
-        if (sigma) sigma[j] = static_cast<float>(sqrt(l > 0.0 ? l : 0.0));
-    }
+    if (lane == 0) row_lam[j] = bounds[2] == 0.0 ? 0.0 : 0.5 * (lo + hi);
 }
 
-// One inverse iteration of vectors j0 .. j0 + nb - 1, a lane each: Gaussian
-// elimination of T - lambda_j with partial pivoting, the right-hand side
-// (the last iterate, |T| scaled; a fixed pseudo-random vector at first)
-// carried along, then back substitution.  S: the rows of the upper factor
-// (reciprocal pivot, two off-diagonals) and the reduced right-hand side, nb
-// of each per row; Z[i][j] the iterates, scale[j] their reciprocal norms.
+// The blocks' eigenvalues in one descending order (ties by row): lam, sigma;
+// order[rank] = row, rank_of[row] = rank.  A single block is in order already,
+// and stays in it where T is not finite (the order of NaNs is no permutation).
+__global__ __launch_bounds__(256) void order_kernel(const double* __restrict__ row_lam, const int2* __restrict__ blk,
+                                                    int n, const double* __restrict__ bounds,
+                                                    double* __restrict__ lam, int* __restrict__ order,
+                                                    int* __restrict__ rank_of, float* __restrict__ sigma) {
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= n) return;
+    const double l = row_lam[j];
+    int rank = j;
+    if (blk[0].y < n && bounds[4] == 0.0) {
+        rank = 0;
+        for (int q = 0; q < n; ++q) {
+            const double v = row_lam[q];
+            rank += v > l || (v == l && q < j);
+        }
+    }
+    lam[rank] = l;
+    order[rank] = j;
+    rank_of[j] = rank;
+    if (sigma) sigma[rank] = static_cast<float>(sqrt(l > 0.0 ? l : 0.0));
+}
+
+// Entry i of start vector j, in [-1, 1): the high half of a Weyl sequence (its
+// steps 2^64 over the golden ratio and over the square root of two) squared
+// twice.
+__device__ __forceinline__ double start_entry(int i, int j) {
+    uint64_t x = (i + 1) * 0x9E3779B97F4A7C15ull + (j + 1) * 0xB504F333F9DE6484ull;
+    x = x * x + x;
+    x = (x >> 32) | (x << 32);
+    x = x * x + x;
+    return static_cast<double>(static_cast<uint32_t>(x >> 32)) * 0x1p-31 - 1.0;
+}
+
+// One inverse iteration of vectors j0 .. j0 + nb - 1, a lane each, on the rows
+// of the vector's block (zero elsewhere): Gaussian elimination of T - shift
+// with partial pivoting, the right-hand side (the last iterate, |T| scaled; a
+// fixed pseudo-random vector at first) carried along, then back substitution.
+// Pivots below the rounding of |T| count as that: the vectors of a cluster
+// would otherwise differ in scale by their ratio and agree in every digit.  S:
+// the rows of the upper factor (reciprocal pivot, two off-diagonals) and the
+// reduced right-hand side, nb of each per row; Z[i][j] the iterates, scale[j]
+// their reciprocal norms.
 __global__ __launch_bounds__(64) void inverse_iteration_kernel(const double* __restrict__ d,
                                                                const double* __restrict__ e, int n,
                                                                const double* __restrict__ bounds,
-                                                               const double* __restrict__ lam, int j0, int nb,
+                                                               const double* __restrict__ row_lam,
+                                                               const int2* __restrict__ blk,
+                                                               const int* __restrict__ order, int j0, int nb,
                                                                int r_max, bool first, double* __restrict__ S,
                                                                double* __restrict__ Z, double* __restrict__ scale) {
     const int t = blockIdx.x * 64 + threadIdx.x;
     if (t >= nb) return;
-    const int j = j0 + t;
+    const int j = j0 + t, row = order[j], beg = blk[row].x, end = blk[row].y;
     const size_t plane = static_cast<size_t>(n) * nb;
     double *U0 = S + t, *U1 = U0 + plane, *U2 = U1 + plane, *Y = U2 + plane;
-    const double norm = bounds[2] > 0.0 ? bounds[2] : 1.0, tiny = 1.1e-16 * norm, l = lam[j];
+    const double norm = bounds[2] > 0.0 ? bounds[2] : 1.0, tiny = 1.1e-16 * norm, apart = kShift * norm;
+    double l = row_lam[row];
+    for (int q = row; q > beg && row_lam[q - 1] - row_lam[q] <= apart; --q) l -= apart;
     const double sc = first ? norm : norm * scale[j];
     auto rhs = [&](int i) -> double {
-        if (!first) return sc * Z[static_cast<size_t>(i) * r_max + j];
-        uint32_t h = static_cast<uint32_t>(i) * 0x9E3779B1u ^ static_cast<uint32_t>(j + 1) * 0x85EBCA77u;
-        h ^= h >> 15; h *= 0x2C1B3C6Du; h ^= h >> 12; h *= 0x297A2D39u; h ^= h >> 15;
-        return sc * (static_cast<double>(h) * 0x1p-31 - 1.0);
+        return sc * (first ? start_entry(i, j) : Z[static_cast<size_t>(i) * r_max + j]);
     };
-    double a = d[0] - l, b = n > 1 ? e[0] : 0.0, y = rhs(0);
+    double a = d[beg] - l, b = beg + 1 < end ? e[beg] : 0.0, y = rhs(beg);
 #pragma unroll 4
-    for (int i = 0; i + 1 < n; ++i) {
-        const double ei = e[i], dn = d[i + 1] - l, en = i + 2 < n ? e[i + 1] : 0.0, yn = rhs(i + 1);
+    for (int i = beg; i + 1 < end; ++i) {
+        const double ei = e[i], dn = d[i + 1] - l, en = i + 2 < end ? e[i + 1] : 0.0, yn = rhs(i + 1);
         const size_t at = static_cast<size_t>(i) * nb;
         const bool keep = fabs(a) >= fabs(ei);
         double pivot = keep ? a : ei;
-        if (pivot == 0.0) pivot = tiny;
+        if (fabs(pivot) < tiny) pivot = copysign(tiny, pivot);
         const double ui = recip_f64(pivot), m = (keep ? ei : a) * ui;
         U0[at] = ui;
         U1[at] = keep ? b : dn;
@@ -438,11 +524,11 @@ __global__ __launch_bounds__(64) void inverse_iteration_kernel(const double* __r
         y = keep ? fma(-m, y, yn) : fma(-m, yn, y);
         a = a2;
     }
-    if (fabs(a) < tiny) a = tiny;
+    if (fabs(a) < tiny) a = copysign(tiny, a);
     double x1 = y * recip_f64(a), x2 = 0.0, ss = x1 * x1;
-    Z[static_cast<size_t>(n - 1) * r_max + j] = x1;
+    Z[static_cast<size_t>(end - 1) * r_max + j] = x1;
 #pragma unroll 4
-    for (int i = n - 2; i >= 0; --i) {
+    for (int i = end - 2; i >= beg; --i) {
         const size_t at = static_cast<size_t>(i) * nb;
         const double x = fma(-U2[at], x2, fma(-U1[at], x1, Y[at])) * U0[at];
         Z[static_cast<size_t>(i) * r_max + j] = x;
@@ -450,47 +536,126 @@ __global__ __launch_bounds__(64) void inverse_iteration_kernel(const double* __r
         x2 = x1;
         x1 = x;
     }
+    for (int i = 0; i < beg; ++i) Z[static_cast<size_t>(i) * r_max + j] = 0.0;
+    for (int i = end; i < n; ++i) Z[static_cast<size_t>(i) * r_max + j] = 0.0;
     scale[j] = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
 }
 
-// Modified Gram-Schmidt within each run of eigenvalues closer than kCluster
-// |T|, one workgroup per run (the others leave at once).  Vectors of
-// eigenvalue zero are multiplied by sigma = 0 afterwards and stay as they are.
-__global__ __launch_bounds__(256) void orthogonalise_kernel(const double* __restrict__ lam,
-                                                            const double* __restrict__ bounds, int n, int r_max,
-                                                            double* __restrict__ Z, double* __restrict__ scale) {
-    __shared__ double red[2][4];
-    const int head = blockIdx.x;
-    const double tol = kCluster * bounds[2];
-    auto close = [&](int m) { return m > 0 && m < r_max && lam[m] > 0.0 && lam[m - 1] - lam[m] <= tol; };
-    if (close(head)) return;
-    int par = 0;
-    for (int m = head + 1; close(m); ++m) {
-        double sm = scale[m];
-        double ss = 0.0;
-        for (int q = head; q < m; ++q) {
-            const double sq = scale[q];
-            double dot = 0.0;
-            for (int i = threadIdx.x; i < n; i += 256) {
-                const size_t at = static_cast<size_t>(i) * r_max;
-                dot = fma(Z[at + m] * sm, Z[at + q] * sq, dot);
-            }
-            dot = block_sum_f64(dot, red[par]);
-            par ^= 1;
-            ss = 0.0;
-            for (int i = threadIdx.x; i < n; i += 256) {
-                const size_t at = static_cast<size_t>(i) * r_max;
-                const double z = fma(-dot, Z[at + q] * sq, Z[at + m] * sm);
-                Z[at + m] = z;
-                ss = fma(z, z, ss);
-            }
-            sm = 1.0;
+// Sums over the wave of 8 values per lane: lane l is left with the sum of value
+// l >> 3 (bits 5, 4, 3 of l choose the halves that it keeps).
+__device__ __forceinline__ double wave_sum8_f64(double (&v)[8]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int h = 4, off = 32; h > 0; h >>= 1, off >>= 1) {
+        const bool upper = lane & off;
+#pragma unroll
+        for (int u = 0; u < h; ++u) {
+            const double keep = upper ? v[u + h] : v[u], give = upper ? v[u] : v[u + h];
+            v[u] = keep + __shfl_xor(give, off, 64);
         }
-        ss = block_sum_f64(ss, red[par]);
-        par ^= 1;
-        if (threadIdx.x == 0) scale[m] = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
-        __syncthreads();
     }
+    double s = v[0];
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    return s;
+}
+
+// The iterates to unit length (scale 1), and those of a block's runs of
+// eigenvalues closer than kCluster |T| orthogonal: classical Gram-Schmidt
+// against 8 vectors at a time, twice (once leaves the rounding that the first
+// pass's cancellation magnified).  One workgroup per run; the vectors of its
+// other ranks leave at once.  Vectors of eigenvalue zero are multiplied by
+// sigma = 0 afterwards and stay as they are.  A thread keeps its CPT entries
+// of the vector in registers and reads the finished ones from rows W[rank][i]
+// of a copy.  Bound by the chain of a run, 2.4 us for each 8 vectors and pass:
+// 1024 x 1024 of rank 4, 252 eigenvalues of rounding size in one run, 46 ms the
+// call (one vector at a time, modified Gram-Schmidt on the columns of Z: 221).
+template <int CPT>
+__global__ __launch_bounds__(256) void orthogonalise_kernel(const double* __restrict__ row_lam,
+                                                            const int2* __restrict__ blk,
+                                                            const int* __restrict__ order,
+                                                            const int* __restrict__ rank_of,
+                                                            const double* __restrict__ bounds, int n, int r_max,
+                                                            double* __restrict__ Z, double* __restrict__ scale,
+                                                            double* W) {
+    constexpr int QB = 8, KEEP = CPT <= 4 ? CPT : 1;   // entries kept between the two uses of a vector
+    __shared__ double red[2][QB][4];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const double tol = kCluster * bounds[2];
+    int s = order[blockIdx.x];
+    const int beg = blk[s].x, end = blk[s].y;
+    auto close = [&](int i) { return i > beg && row_lam[i] > 0.0 && row_lam[i - 1] - row_lam[i] <= tol; };
+    if (close(s)) return;
+    const int head = s;
+    int par = 0;
+    double z[CPT];
+    do {
+        const int m = rank_of[s];
+        const double sm = scale[m];
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            const int i = tid + 256 * c;
+            z[c] = i < n ? sm * Z[static_cast<size_t>(i) * r_max + m] : 0.0;
+        }
+        for (int pass = 0; pass < 2 && s > head; ++pass) {
+            for (int q0 = head; q0 < s; q0 += QB) {
+                const double* row[QB];
+                double w[QB][KEEP], dot[QB];
+#pragma unroll
+                for (int u = 0; u < QB; ++u) {
+                    row[u] = W + static_cast<size_t>(rank_of[min(q0 + u, s - 1)]) * n;
+                    dot[u] = 0.0;
+                }
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) {
+                    const int i = min(tid + 256 * c, n - 1);     // z[c] is 0 past n
+#pragma unroll
+                    for (int u = 0; u < QB; ++u) {
+                        const double v = row[u][i];
+                        dot[u] = fma(z[c], v, dot[u]);
+                        if (KEEP == CPT) w[u][c < KEEP ? c : 0] = v;
+                    }
+                }
+                const double d = wave_sum8_f64(dot);
+                if ((lane & 7) == 0) red[par][lane >> 3][tid >> 6] = d;
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < QB; ++u) {
+                    const double* r = red[par][u];
+                    dot[u] = q0 + u < s ? (r[0] + r[1]) + (r[2] + r[3]) : 0.0;
+                }
+                par ^= 1;
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) {
+                    const int i = min(tid + 256 * c, n - 1);
+                    double v = z[c];
+#pragma unroll
+                    for (int u = 0; u < QB; ++u)
+                        v = fma(-dot[u], KEEP == CPT ? w[u][c < KEEP ? c : 0] : row[u][i], v);
+                    z[c] = tid + 256 * c < n ? v : 0.0;
+                }
+            }
+            double ss = 0.0;
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) ss = fma(z[c], z[c], ss);
+            ss = block_sum_f64(ss, red[par][0]);
+            par ^= 1;
+            const double inv = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) z[c] *= inv;
+        }
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            const int i = tid + 256 * c;
+            if (i < n) {
+                Z[static_cast<size_t>(i) * r_max + m] = z[c];
+                W[static_cast<size_t>(m) * n + i] = z[c];
+            }
+        }
+        __syncthreads();                         // the row of W is there, and scale[m] was read
+        if (tid == 0) scale[m] = 1.0;
+        ++s;
+    } while (s < end && close(s) && rank_of[s] < r_max);
 }
 
 // X = Q Z: the reflectors applied in reverse to vector j, one workgroup each,
@@ -500,12 +665,10 @@ template <int CPT>
 __global__ __launch_bounds__(256) void back_transform_kernel(const double* __restrict__ V,
                                                              const double* __restrict__ tau, int n, int r_max,
                                                              const double* __restrict__ Z,
-                                                             const double* __restrict__ scale,
                                                              double* __restrict__ Xr) {
     __shared__ double red[2][4];
     const int j = blockIdx.x, tid = threadIdx.x;
     double z[CPT], v[CPT];
-    const double sc = scale[j];
     auto load = [&](int k) {
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
@@ -516,7 +679,7 @@ __global__ __launch_bounds__(256) void back_transform_kernel(const double* __res
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
         const int i = tid + 256 * c;
-        z[c] = i < n ? sc * Z[static_cast<size_t>(i) * r_max + j] : 0.0;
+        z[c] = i < n ? Z[static_cast<size_t>(i) * r_max + j] : 0.0;
     }
     if (n > 2) load(n - 3);
     for (int k = n - 3; k >= 0; --k) {
@@ -648,7 +811,10 @@ hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uin
     double *E = at(l.E), *C = at(l.C), *V = at(l.V), *tau = at(l.tau), *lam = at(l.lam), *d = at(l.d), *e = at(l.e);
     double *p[2] = {at(l.p), at(l.p) + n}, *bounds = at(l.bounds), *scale = at(l.scale), *sign = at(l.sign);
     double *Xr = at(l.Xr), *P = at(l.P);
+    double* row_lam = at(l.row_lam);
     double2* de = reinterpret_cast<double2*>(base + l.de);
+    int2* blk = reinterpret_cast<int2*>(base + l.blk);
+    int *order = reinterpret_cast<int*>(base + l.order), *rank_of = reinterpret_cast<int*>(base + l.rank_of);
     hipError_t err;
 
     const size_t total = static_cast<size_t>(d_out) * d_in;
@@ -667,8 +833,10 @@ hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uin
                                p[k & 1], p[(k & 1) ^ 1], tau, d, e);
         });
     }
-    hipLaunchKernelGGL(tridiagonal_prep_kernel, dim3(1), dim3(256), 0, st, d, e, n, de, bounds);
-    hipLaunchKernelGGL(bisect_kernel, dim3((n + 3) / 4), dim3(256), 0, st, de, n, bounds, lam, sigma);
+    hipLaunchKernelGGL(tridiagonal_prep_kernel, dim3(1), dim3(256), 0, st, d, e, n, de, blk, bounds);
+    hipLaunchKernelGGL(bisect_kernel, dim3((n + 3) / 4), dim3(256), 0, st, de, blk, n, bounds, row_lam);
+    hipLaunchKernelGGL(order_kernel, dim3(grid1(n)), dim3(256), 0, st, row_lam, blk, n, bounds, lam, order, rank_of,
+                       sigma);
     if (r_max > 0) {
         // C is free now: the eliminations of n / 4 vectors at a time (4 planes
         // of n each), the iterates in P until the product with E needs it
@@ -677,13 +845,16 @@ hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uin
             for (int j0 = 0; j0 < r_max; j0 += batch) {
                 const int nb = r_max - j0 < batch ? r_max - j0 : batch;
                 hipLaunchKernelGGL(inverse_iteration_kernel, dim3((nb + 63) / 64), dim3(64), 0, st, d, e, n, bounds,
-                                   lam, j0, nb, r_max, sweep == 0, C, P, scale);
+                                   row_lam, blk, order, j0, nb, r_max, sweep == 0, C, P, scale);
             }
-            hipLaunchKernelGGL(orthogonalise_kernel, dim3(r_max), dim3(256), 0, st, lam, bounds, n, r_max, P, scale);
+            by_columns(n, [&](auto cpt) {
+                hipLaunchKernelGGL((orthogonalise_kernel<decltype(cpt)::value>), dim3(r_max), dim3(256), 0, st, row_lam,
+                                   blk, order, rank_of, bounds, n, r_max, P, scale, Xr);
+            });
         }
         by_columns(n, [&](auto cpt) {
             hipLaunchKernelGGL((back_transform_kernel<decltype(cpt)::value>), dim3(r_max), dim3(256), 0, st, V, tau, n,
-                               r_max, P, scale, Xr);
+                               r_max, P, Xr);
         });
     }
     if ((err = hipGetLastError()) != hipSuccess) return err;

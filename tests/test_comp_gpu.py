@@ -288,3 +288,51 @@ def test_repeated_and_zero_singular_values(spectra, r_max):
     E = _known_spectrum(64, 128, [np.asarray(s) * scale for s in spectra], 7)
     A, B, sigma = _build(E, r_max)
     _check_known(E, s_ref, A, B, sigma, r_max)
+
+
+def _coupled(kind, t):
+    """Residuals whose Gram matrix is block-diagonal but for couplings of size
+    t (tiny, or graded where t is 0), so that eigenvalues repeat to rounding in
+    blocks that hang together by less than that."""
+    g = np.random.default_rng(17)
+    if kind == "identity":
+        return np.eye(64, 128) + t * g.standard_normal((64, 128)), 64
+    if kind == "three values":
+        n, big = 128, 256
+        return np.diag(g.choice([0.5, 1.0, 1.5], n)) @ np.eye(n, big) + t * g.standard_normal((n, big)), 32
+    n, big = 96, 128
+    i, j = np.indices((n, big))
+    if kind == "band":
+        return np.where(i == j, 1.0 + i % 4,
+                        np.where(((i + j) % 3 == 0) & (abs(i - j) < 4), t * g.standard_normal((n, big)), 0.0)), 96
+    if kind == "pairs":         # couplings 1e-2 .. 1e-21
+        return np.where(i == j, np.where(i % 2, 1.0, 1.5),
+                        np.where((i % 2 == 0) & (j == i + 1), 10.0 ** (-2.0 - (i // 2) % 20), 0.0)), 60
+    assert kind == "chain"      # couplings just past the rounding
+    return np.where(i == j, 1.0, np.where(j == i + 1, 3e-14, 0.0)), 96
+
+
+@pytest.mark.parametrize("kind,t", [(k, t) for k in ("identity", "three values", "band")
+                                    for t in (1e-20, 1e-26, 1e-30, 1e-34, 1e-37)] + [("pairs", 0.0), ("chain", 0.0)])
+def test_couplings_below_the_rounding_of_a_repeated_value(kind, t):
+    E, r_max = _coupled(kind, t)
+    E = np.ascontiguousarray(E, dtype=np.float32)
+    s_ref = np.linalg.svd(E.astype(np.float64), compute_uv=False)
+    A, B, sigma = _build(E, r_max)
+    _check_known(E, s_ref, A, B, sigma, r_max)
+
+
+@pytest.mark.parametrize("n,big,r_max", [(64, 128, 64), (300, 384, 256), (700, 768, 130), (2100, 2176, 40), (4200, 4224, 12)])
+def test_equal_singular_values_in_one_run(n, big, r_max):
+    """A random orthogonal matrix in fp32: one run of eigenvalues a rounding of
+    fp32 apart, so all r_max vectors are orthogonalised, at each number of
+    entries a thread keeps."""
+    g = np.random.default_rng(n)
+    m = min(n, 300)
+    E = np.zeros((n, big))
+    for at in range(0, n, m):
+        k = min(m, n - at)
+        E[at:at + k, at:at + k] = np.linalg.qr(g.standard_normal((k, k)))[0]
+    E = np.ascontiguousarray(E[g.permutation(n)][:, g.permutation(big)], dtype=np.float32)
+    A, B, sigma = _build(E, r_max)
+    _check_known(E, np.ones(n), A, B, sigma, r_max)
