@@ -138,10 +138,13 @@ cl_status cl_dequantize(const cl_qweight* w, float* W_hat, void* stream);
  * Computed in fp64 from the Gram matrix of E over its smaller side, reduced
  * to tridiagonal form by Householder reflectors, with eigenvalues by bisection
  * and the leading r_max vectors by inverse iteration; singular values far
- * below 1e-8 * sigma[0] have absolute accuracy only.  An offline step: the
- * call waits on the stream once, after the eigensolver, and returns when the
- * factors are enqueued.  Limits: min(d_out, d_in) <= 8192, d_out * d_in <=
- * 2^31 (CL_EUNSUPPORTED beyond).
+ * below 1e-8 * sigma[0] have absolute accuracy only.  The vectors are checked
+ * (|T z - lambda z| and their inner products) and iterated further where they
+ * do not pass.  An offline step: the call waits on the stream for the check,
+ * once as a rule, and returns when the factors are enqueued.  Limits:
+ * min(d_out, d_in) <= 8192, d_out * d_in <= 2^31 (CL_EUNSUPPORTED beyond);
+ * CL_EUNSUPPORTED also, with A and B not written, for a residual that is not
+ * finite and if the vectors do not pass in 8 sweeps.
  */
 cl_status cl_build_compensation(const float* W, const cl_qweight* w, int32_t r_max, uint16_t* A, uint16_t* B,
                                 float* sigma, void* ws, size_t ws_bytes, void* stream);
@@ -151,8 +154,9 @@ size_t cl_build_compensation_workspace(int32_t d_out, int32_t d_in, int32_t r_ma
 
 /*
  * Sweeps over the eigenvectors that the calling thread's last
- * cl_build_compensation call ran (1 for r_max = 0; 0 before any call).  A
- * report of the eigensolver's work, for timing and tuning.
+ * cl_build_compensation call ran: 2, or as many more as the check asked for
+ * (1 for r_max = 0; 0 before any call and for a residual that is not finite).
+ * A report of the eigensolver's work, for timing and tuning.
  */
 int32_t cl_build_compensation_sweeps(void);
 

@@ -658,7 +658,8 @@ def build_compensation_sweeps():
 def build_compensation(W, w, r_max, stream=None):
     """``cl_build_compensation``: fp32 weight ``W`` [d_out][d_in] and its
     packed backbone ``w`` -> ``(A fp16 [r_max][d_in], B fp16 [d_out][r_max],
-    sigma fp32 [min(d_out, d_in)])``.  Waits on the stream once."""
+    sigma fp32 [min(d_out, d_in)])``.  Waits on the stream for the check of the
+    eigenvectors (once as a rule)."""
     A = torch.empty((r_max, w.d_in), dtype=torch.float16, device=W.device)
     B = torch.empty((w.d_out, r_max), dtype=torch.float16, device=W.device)
     sigma = torch.empty((min(w.d_out, w.d_in),), dtype=torch.float32, device=W.device)

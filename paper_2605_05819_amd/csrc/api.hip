@@ -132,6 +132,10 @@ cl_status cl_build_compensation(const float* W, const cl_qweight* w, int32_t r_m
     const hipError_t e = cl::launch_build_compensation(W, qw, r_max, A, B, sigma, ws,
                                                        static_cast<hipStream_t>(stream), &sweeps);
     g_last_sweeps = sweeps;
+    if (e == hipErrorNotReady && sweeps == 0)
+        return fail(CL_EUNSUPPORTED, "%s: the residual W - deq(q) is not finite", who);
+    if (e == hipErrorNotReady)
+        return fail(CL_EUNSUPPORTED, "%s: the eigenvectors did not converge in %d sweeps", who, sweeps);
     return hip_status(e, who);
 }
 

@@ -41,7 +41,9 @@ hipError_t launch_linear_prefill(const QW& w, const LR& c, const void* X, int M,
                                  void* ws, hipStream_t st);
 
 // Compensation factors from the SVD of W - deq(Q) (fp64 Gram matrix and
-// tridiagonal eigensolver); synchronizes the stream once.
+// tridiagonal eigensolver); synchronizes the stream once per check of the
+// eigenvectors.  hipErrorNotReady: the residual is not finite (0 sweeps) or the
+// vectors did not pass within the sweep limit.
 bool comp_fits(int d_out, int d_in);
 size_t comp_workspace_bytes(int d_out, int d_in, int r_max);
 hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uint16_t* A, uint16_t* B, float* sigma,

@@ -46,7 +46,11 @@ namespace {
 
 // Sweep 1 leaves |T| eps / gap of the neighbours in a vector, sweep 2 its square
 // (an unlucky start vector included).
-constexpr int kInverseSweeps = 2;
+constexpr int kInverseSweeps = 2, kMaxSweeps = 8;
+// What the vectors are checked for after a sweep: |T z - lambda z| relative to
+// |T|, and the inner products of different ones.  Ordinary residuals reach 1e-15
+// and eps / gap; 175,000 near-degenerate ones on the CPU 2e-12 and 6e-10.
+constexpr double kResidualTol = 1e-10, kOrthogonalTol = 1e-8;
 // Bisection rounds: 65-section of an interval of width 2 |T| down to 2^-53 |T|.
 constexpr int kSections = 9;
 // Eigenvalues of a block closer than this (relative to |T|) have their vectors
@@ -345,7 +349,7 @@ __global__ __launch_bounds__(256) void householder_step_kernel(double* __restric
 // The couplings within the rounding dropped (e set to zero); blk[i] = the rows
 // of i's block; (d_i, e_i-1^2) pairs for the Sturm counts; bounds = {lower and
 // upper end of the Gershgorin discs, |T|, smallest pivot, 1 if T is not
-// finite}.  One workgroup, a run of rows per thread.
+// finite, (check_kernel's) worst check over its tolerance}.  One workgroup, a run of rows per thread.
 __global__ __launch_bounds__(256) void tridiagonal_prep_kernel(const double* __restrict__ d, double* __restrict__ e,
                                                                int n, double2* __restrict__ de,
                                                                int2* __restrict__ blk, double* __restrict__ bounds) {
@@ -405,6 +409,7 @@ __global__ __launch_bounds__(256) void tridiagonal_prep_kernel(const double* __r
         bounds[2] = norm;
         bounds[3] = 2.3e-308 * fmax(1.0, em[0]);
         bounds[4] = odd[0];
+        bounds[5] = 0.0;
     }
 }
 
@@ -488,13 +493,14 @@ __device__ __forceinline__ double start_entry(int i, int j) {
 // their reciprocal norms.
 __global__ __launch_bounds__(64) void inverse_iteration_kernel(const double* __restrict__ d,
                                                                const double* __restrict__ e, int n,
-                                                               const double* __restrict__ bounds,
+                                                               double* __restrict__ bounds,
                                                                const double* __restrict__ row_lam,
                                                                const int2* __restrict__ blk,
                                                                const int* __restrict__ order, int j0, int nb,
                                                                int r_max, bool first, double* __restrict__ S,
                                                                double* __restrict__ Z, double* __restrict__ scale) {
     const int t = blockIdx.x * 64 + threadIdx.x;
+    if (t == 0) bounds[5] = 0.0;                  // the check that follows the sweep
     if (t >= nb) return;
     const int j = j0 + t, row = order[j], beg = blk[row].x, end = blk[row].y;
     const size_t plane = static_cast<size_t>(n) * nb;
@@ -656,6 +662,35 @@ __global__ __launch_bounds__(256) void orthogonalise_kernel(const double* __rest
         if (tid == 0) scale[m] = 1.0;
         ++s;
     } while (s < end && close(s) && rank_of[s] < r_max);
+}
+
+// bounds[5] = the worst of vector j's |T z - lambda z| / |T| and of its inner
+// products Gm[j][k] with the others, each over its tolerance (products with
+// vectors of eigenvalue zero apart); 1e300 where one is not a number.  One
+// workgroup per vector; the bits of a positive double are in its order.
+__global__ __launch_bounds__(256) void check_kernel(const double* __restrict__ d, const double* __restrict__ e, int n,
+                                                    const double* __restrict__ lam, int r_max,
+                                                    const double* __restrict__ Z, const double* __restrict__ Gm,
+                                                    double* __restrict__ bounds) {
+    __shared__ double red[4];
+    const int j = blockIdx.x, tid = threadIdx.x;
+    const double norm = bounds[2] > 0.0 ? bounds[2] : 1.0, l = lam[j];
+    auto z = [&](int i) { return Z[static_cast<size_t>(i) * r_max + j]; };
+    double ss = 0.0;
+    for (int i = tid; i < n; i += 256) {
+        double v = (d[i] - l) * z(i);
+        if (i > 0) v = fma(e[i - 1], z(i - 1), v);
+        if (i + 1 < n) v = fma(e[i], z(i + 1), v);
+        ss = fma(v, v, ss);
+    }
+    ss = block_sum_f64(ss, red);
+    double worst = sqrt(ss) / (norm * kResidualTol);
+    if (tid < r_max && (tid == j || (l > 0.0 && lam[tid] > 0.0))) {
+        const double g = fabs(Gm[static_cast<size_t>(j) * r_max + tid] - (tid == j ? 1.0 : 0.0)) / kOrthogonalTol;
+        worst = g <= worst ? worst : g;
+    }
+    if (!(worst < 1e300)) worst = 1e300;
+    atomicMax(reinterpret_cast<unsigned long long*>(bounds + 5), __builtin_bit_cast(unsigned long long, worst));
 }
 
 // X = Q Z: the reflectors applied in reverse to vector j, one workgroup each,
@@ -837,30 +872,47 @@ hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uin
     hipLaunchKernelGGL(bisect_kernel, dim3((n + 3) / 4), dim3(256), 0, st, de, blk, n, bounds, row_lam);
     hipLaunchKernelGGL(order_kernel, dim3(grid1(n)), dim3(256), 0, st, row_lam, blk, n, bounds, lam, order, rank_of,
                        sigma);
-    if (r_max > 0) {
+    // sweeps of inverse iteration, two at first and then one at a time, until
+    // the vectors pass the check; each time the host waits for its outcome (W
+    // has been read then, and a fault of the work so far is reported by this call)
+    int sweeps = 0;
+    do {
         // C is free now: the eliminations of n / 4 vectors at a time (4 planes
-        // of n each), the iterates in P until the product with E needs it
-        const int batch = n < 4 ? 1 : n / 4;
-        for (int sweep = 0; sweep < kInverseSweeps; ++sweep) {
+        // of n each); the iterates in P until the product with E needs it, the
+        // finished ones row by row, then their products, in Xr
+        const int batch = n < 4 ? 1 : n / 4, until = sweeps == 0 ? kInverseSweeps : sweeps + 1;
+        for (; r_max > 0 && sweeps < until; ++sweeps) {
             for (int j0 = 0; j0 < r_max; j0 += batch) {
                 const int nb = r_max - j0 < batch ? r_max - j0 : batch;
                 hipLaunchKernelGGL(inverse_iteration_kernel, dim3((nb + 63) / 64), dim3(64), 0, st, d, e, n, bounds,
-                                   row_lam, blk, order, j0, nb, r_max, sweep == 0, C, P, scale);
+                                   row_lam, blk, order, j0, nb, r_max, sweeps == 0, C, P, scale);
             }
             by_columns(n, [&](auto cpt) {
                 hipLaunchKernelGGL((orthogonalise_kernel<decltype(cpt)::value>), dim3(r_max), dim3(256), 0, st, row_lam,
                                    blk, order, rank_of, bounds, n, r_max, P, scale, Xr);
             });
         }
-        by_columns(n, [&](auto cpt) {
-            hipLaunchKernelGGL((back_transform_kernel<decltype(cpt)::value>), dim3(r_max), dim3(256), 0, st, V, tau, n,
-                               r_max, P, Xr);
-        });
-    }
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    // W has been read, and a fault of the work so far is reported by this call
-    if ((err = hipStreamSynchronize(st)) != hipSuccess) return err;
-    if (sweeps_out) *sweeps_out = r_max > 0 ? kInverseSweeps : 1;
+        if (r_max > 0) {
+            gemm<false, false>(P, 1, r_max, P, 1, r_max, r_max, r_max, n, Xr, r_max, st);
+            hipLaunchKernelGGL(check_kernel, dim3(r_max), dim3(256), 0, st, d, e, n, lam, r_max, P, Xr, bounds);
+            by_columns(n, [&](auto cpt) {
+                hipLaunchKernelGGL((back_transform_kernel<decltype(cpt)::value>), dim3(r_max), dim3(256), 0, st, V, tau,
+                                   n, r_max, P, Xr);
+            });
+        }
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+        double state[2];                          // T not finite; the worst check
+        if ((err = hipMemcpyAsync(state, bounds + 4, sizeof(state), hipMemcpyDeviceToHost, st)) != hipSuccess)
+            return err;
+        if ((err = hipStreamSynchronize(st)) != hipSuccess) return err;
+        *sweeps_out = r_max > 0 ? sweeps : 1;
+        if (state[0] != 0.0) {
+            *sweeps_out = 0;
+            return hipErrorNotReady;
+        }
+        if (r_max == 0 || state[1] <= 1.0) break;
+        if (sweeps == kMaxSweeps) return hipErrorNotReady;
+    } while (true);
 
     if (r_max > 0) {
         if (right) {
