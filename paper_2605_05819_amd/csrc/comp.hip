@@ -23,8 +23,8 @@
 //     reduction's rounding; every eigenvalue of each block by bisection on
 //     Sturm counts, 64 points of an interval per wave and round; eigenvectors
 //     of the blocks by inverse iteration, one lane per vector, with the
-//     vectors of a block's close eigenvalues orthogonalised among each other;
-//     X = Q Z.
+//     vectors of a block's close eigenvalues orthogonalised among each other
+//     and all of them then made orthonormal to rounding; X = Q Z.
 //  4. sigma = sqrt(lambda), descending.  If X holds right vectors V:
 //     A = sqrt(sigma) V^T and
 //     B = E V / sqrt(sigma) (= U sqrt(sigma)); if it holds left vectors U:
@@ -55,7 +55,7 @@ constexpr double kResidualTol = 1e-10, kOrthogonalTol = 1e-8;
 constexpr int kSections = 9;
 // Eigenvalues of a block closer than this (relative to |T|) have their vectors
 // orthogonalised; beyond it inverse iteration alone leaves them orthogonal to
-// better than 1e-9, far below the rounding of the fp16 factors.
+// better than 1e-9, which the last step (check_kernel) squares.
 constexpr double kCluster = 1e-6;
 // A coupling e_i is dropped, and T falls into two blocks there, where it is
 // within kDrop sqrt(n) (|d_i| + |d_i+1|): the rounding of the n reflectors
@@ -666,11 +666,13 @@ __global__ __launch_bounds__(256) void orthogonalise_kernel(const double* __rest
 
 // bounds[5] = the worst of vector j's |T z - lambda z| / |T| and of its inner
 // products Gm[j][k] with the others, each over its tolerance (products with
-// vectors of eigenvalue zero apart); 1e300 where one is not a number.  One
-// workgroup per vector; the bits of a positive double are in its order.
+// vectors of eigenvalue zero apart); 1e300 where one is not a number.  Gm is
+// left as (3 I - Gm) / 2: Z times it is orthonormal to the square of Z's own
+// error, 1e-9 to 1e-18 (one step of Newton's iteration for the polar factor).
+// One workgroup per vector; the bits of a positive double are in its order.
 __global__ __launch_bounds__(256) void check_kernel(const double* __restrict__ d, const double* __restrict__ e, int n,
                                                     const double* __restrict__ lam, int r_max,
-                                                    const double* __restrict__ Z, const double* __restrict__ Gm,
+                                                    const double* __restrict__ Z, double* __restrict__ Gm,
                                                     double* __restrict__ bounds) {
     __shared__ double red[4];
     const int j = blockIdx.x, tid = threadIdx.x;
@@ -685,9 +687,13 @@ __global__ __launch_bounds__(256) void check_kernel(const double* __restrict__ d
     }
     ss = block_sum_f64(ss, red);
     double worst = sqrt(ss) / (norm * kResidualTol);
-    if (tid < r_max && (tid == j || (l > 0.0 && lam[tid] > 0.0))) {
-        const double g = fabs(Gm[static_cast<size_t>(j) * r_max + tid] - (tid == j ? 1.0 : 0.0)) / kOrthogonalTol;
-        worst = g <= worst ? worst : g;
+    if (tid < r_max) {
+        double* g = Gm + static_cast<size_t>(j) * r_max + tid;
+        const double one = tid == j ? 1.0 : 0.0;
+        const double off = tid == j || (l > 0.0 && lam[tid] > 0.0) ? *g - one : 0.0;
+        *g = fma(-0.5, off, one);
+        const double o = fabs(off) / kOrthogonalTol;
+        worst = o <= worst ? worst : o;
     }
     if (!(worst < 1e300)) worst = 1e300;
     atomicMax(reinterpret_cast<unsigned long long*>(bounds + 5), __builtin_bit_cast(unsigned long long, worst));
@@ -879,7 +885,8 @@ hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uin
     do {
         // C is free now: the eliminations of n / 4 vectors at a time (4 planes
         // of n each); the iterates in P until the product with E needs it, the
-        // finished ones row by row, then their products, in Xr
+        // finished ones row by row, then their products, in Xr; the
+        // orthonormal ones in C
         const int batch = n < 4 ? 1 : n / 4, until = sweeps == 0 ? kInverseSweeps : sweeps + 1;
         for (; r_max > 0 && sweeps < until; ++sweeps) {
             for (int j0 = 0; j0 < r_max; j0 += batch) {
@@ -895,9 +902,10 @@ hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uin
         if (r_max > 0) {
             gemm<false, false>(P, 1, r_max, P, 1, r_max, r_max, r_max, n, Xr, r_max, st);
             hipLaunchKernelGGL(check_kernel, dim3(r_max), dim3(256), 0, st, d, e, n, lam, r_max, P, Xr, bounds);
+            gemm<true, false>(P, r_max, 1, Xr, 1, r_max, n, r_max, r_max, C, r_max, st);
             by_columns(n, [&](auto cpt) {
                 hipLaunchKernelGGL((back_transform_kernel<decltype(cpt)::value>), dim3(r_max), dim3(256), 0, st, V, tau,
-                                   n, r_max, P, Xr);
+                                   n, r_max, C, Xr);
             });
         }
         if ((err = hipGetLastError()) != hipSuccess) return err;

@@ -12,6 +12,8 @@ sets are correct when singular values nearly coincide, so parity is:
 Shapes cover d_out > d_in, d_out < d_in, odd sizes, full rank, 2/4-bit, the
 1024 x 1024 rank-16 linear and an all-zero residual."""
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -355,3 +357,37 @@ def test_a_residual_that_is_not_finite_is_an_error(value, n, big, r_max):
     A, B, sigma = _build(E, r_max)
     s_ref = np.linalg.svd(E.astype(np.float64), compute_uv=False)
     _check_known(E, s_ref, A, B, sigma, r_max)
+
+
+@pytest.mark.parametrize("kind", ["random", "triples", "gaps"])
+def test_the_fp64_vectors_are_orthonormal_to_rounding(kind):
+    """The eigenvectors that the factors are scaled from, fp64 rows of n in the
+    workspace ahead of its last array (r_max rows of the larger side), each
+    array padded to 256 bytes.  Gaps of 3e-6 |T| leave inverse iteration alone
+    at 1e-12 and chains of near-equal values at 1e-11; inner products of n
+    terms round by n 2^-53."""
+    g = np.random.default_rng(3)
+    i, j = np.indices((96, 128))
+    if kind == "random":
+        E, r = g.standard_normal((512, 1024)), 128
+    elif kind == "triples":
+        E, r = np.where(i == j, np.where(i % 3 == 1, 1.0, 1.5),
+                        np.where((i % 3 != 2) & (j == i + 1), 10.0 ** (-2.0 - (i // 3) % 12), 0)), 96
+    else:
+        s = np.concatenate([1 - 3e-6 * np.arange(32), np.linspace(0.9, 0.1, 32)])
+        U, V = (np.linalg.qr(g.standard_normal((64, 64)))[0] for _ in range(2))
+        E, r = (U * s) @ V @ np.eye(64, 128), 48
+    E = torch.from_numpy(np.ascontiguousarray(E, dtype=np.float32)).cuda()
+    n, big = E.shape
+    z = torch.zeros((n, big // 128), dtype=torch.float16, device="cuda")
+    w = cl.QWeight(torch.zeros((n, big // 8), dtype=torch.int32, device="cuda"), z, z.clone(), n, big, 4, 128).c()
+    A = torch.empty((r, big), dtype=torch.float16, device="cuda")
+    B = torch.empty((n, r), dtype=torch.float16, device="cuda")
+    need = cl.lib().cl_build_compensation_workspace(n, big, r)
+    ws = torch.zeros(need, dtype=torch.uint8, device="cuda")
+    assert cl.lib().cl_build_compensation(E.data_ptr(), ctypes.byref(w), r, A.data_ptr(), B.data_ptr(), None,
+                                          ws.data_ptr(), need, None) == 0
+    torch.cuda.synchronize()
+    padded = [(8 * r * m + 8 + 255) // 256 * 256 for m in (n, big)]
+    X = ws[need - sum(padded):][:8 * r * n].view(torch.float64).view(r, n).cpu().numpy()
+    assert np.abs(X @ X.T - np.eye(r)).max() <= n * 2.0 ** -53 + 1e-15
