@@ -84,8 +84,8 @@ constexpr int direct_batches(int lg, int cpl) { return cpl == 2 ? 2 : (lg == 64 
 // the tiles in flight per wave.
 constexpr int kStreamBlocks = 512;
 constexpr int kStreamDepth = 2;
-constexpr int kStreamMaxRows = (1 << 29) / kMaxSlots - 1;   // 31-bit byte offsets of fp32 outputs
 constexpr int kStreamMinExperts = 32, kStreamMinWidth = 36 << 10;
+constexpr int kStreamMaxRows = (1 << 29) / kMaxSlots - 1;   // 31-bit byte offsets of fp32 outputs
 // Gated calls off the one-launch path form SiLU(g) u in the preparation, once
 // per workgroup that reads the slot, up to this width (128 experts of 768: a
 // kernel of its own took 4.7 us of a layer); on wider rows the repeated
@@ -126,8 +126,9 @@ struct MoeArgs {
     int E, T, k, d_in, G, act, out, x_per_slot;
     // workspace
     int* n_active;
-    int* table;              // [max_active][kTab]: expert, first sorted index, slot count, first slot,
+    int* table;              // [max_active + S / 16][kTab]: expert, first sorted index, slot count, first slot,
                              // then each linear's rank, then its first 16 slots (padded with the first)
+    int split;               // an entry for every 16 slots of an expert (n_active counts those)
     int* sorted;             // [T*k] slot ids grouped by expert, slot order within
     f16x2* xp;               // [rows][d_in/2]
     float* sx;               // [rows][chunks]
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
     extern __shared__ int prep_lds[];
     __shared__ int wsum[4][2];
     __shared__ int wcnt[4];
-    __shared__ int sel, sel_lt, sel_n, srank;
+    __shared__ int sel, sel_lt, sel_n, sel_at, srank;
     __shared__ f32x4 tred[4][64];          // the waves' K parts of a 16 x 16 tile of t
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -207,7 +208,8 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
             const int ex = 4 * tid + q;
             c[q] = ex < a.E ? hist[ex] : 0;
             cs += c[q];
-            fs += c[q] > 0;
+            // routed experts, and table entries in the upper half
+            fs += c[q] > 0 ? 1 + ((a.split ? (c[q] + 15) / 16 : 1) << 16) : 0;
         }
         int ic = cs, ifl = fs;                   // inclusive scan within the wave
         for (int off = 1; off < 64; off <<= 1) {
@@ -221,13 +223,13 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if (c[q] > 0) {
-                if (pf == j) { sel = 4 * tid + q; sel_lt = pc; sel_n = c[q]; }
+                if ((pf & 0xffff) == j) { sel = 4 * tid + q; sel_lt = pc; sel_n = c[q]; sel_at = pf >> 16; }
                 pc += c[q];
-                pf += 1;
+                pf += 1 + ((a.split ? (c[q] + 15) / 16 : 1) << 16);
             }
         }
         if (li == 0 && j == 0 && quad == 0 && tid == 0)
-            *a.n_active = wsum[0][1] + wsum[1][1] + wsum[2][1] + wsum[3][1];
+            *a.n_active = (wsum[0][1] + wsum[1][1] + wsum[2][1] + wsum[3][1]) >> 16;
         __syncthreads();
         if (j == 0 && quad == 0) {
             // out-of-range ids: their output rows are zero.  One parallel
@@ -254,6 +256,7 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
         const int e = sel;
         if (e < 0) return;                      // fewer than j + 1 routed experts
         const int ne = sel_n, cnt_lt = sel_lt;
+        int* const ent = a.table + kTab * sel_at;
         int rank = rk[e];
         rank = rank < 0 ? 0 : (rank > L.r_max ? L.r_max : rank);
         // per-slot ranks: the expert's rank here is the largest of its slots'
@@ -275,13 +278,14 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
                 const int pos = off + __popcll(m & ((1ull << lane) - 1ull));
                 if (li == 0 && quad == 0) {
                     a.sorted[cnt_lt + pos] = sl;
-                    if (pos == 0) a.table[kTab * j + 3] = sl;
-                }
-                if (li == 0 && quad == 0) {
                     // entries 8 + pos, and past the last slot the first again
-                    if (pos < 16) a.table[kTab * j + 8 + pos] = sl;
-                    if (pos == 0)
-                        for (int u = ne; u < 16; ++u) a.table[kTab * j + 8 + u] = sl;
+                    const int part = a.split ? pos >> 4 : 0, at = pos - 16 * part;
+                    int* const pe = ent + kTab * part;
+                    if (at < 16) pe[8 + at] = sl;
+                    if (at == 0) {
+                        pe[3] = sl;
+                        for (int u = ne - 16 * part; u < 16; ++u) pe[8 + u] = sl;
+                    }
                 }
                 mys[pos] = sl;
                 if (dyn) {
@@ -294,12 +298,15 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
         }
         if (dyn) rank = srank;
         if (quad == 0 && tid == 0) {
-            if (li == 0) {
-                a.table[kTab * j + 0] = e;
-                a.table[kTab * j + 1] = cnt_lt;
-                a.table[kTab * j + 2] = ne;
+            for (int first = 0; first < (a.split ? ne : 1); first += 16) {
+                int* const pe = ent + kTab * (first / 16);
+                if (li == 0) {
+                    pe[0] = e;
+                    pe[1] = cnt_lt + first;
+                    pe[2] = a.split ? min(16, ne - first) : ne;
+                }
+                pe[4 + li] = rank;
             }
-            a.table[kTab * j + 4 + li] = rank;
         }
         // t[slot][i] = A_e[i] . x_slot for 16 slots and 16 rank rows at a
         // time on v_mfma_f32_16x16x32_f16 (slots the A operand, rows of A_e
@@ -928,25 +935,29 @@ __device__ __forceinline__ void buffer_store_out(void* y, uint32_t n, int idx, f
 // The 4-bit backbone off the one-launch path, rows of at most 4096 codes: the
 // expert's rows against its slots on v_mfma_f32_16x16x32_f16, streamed.
 // Bound by HBM (the routed experts' codes).  The tiles of 16 rows of every
-// routed expert and linear form one list (expert, linear, tile) that the
-// resident workgroups share evenly: a workgroup's start (table entries, slot
-// ids, activations: three dependent round trips) is paid once or twice per
-// call instead of once per 64 rows, and no last wave of workgroups is nearly
-// empty.  A workgroup's waves split K into KW = a.ks parts of NBK 128-code
+// routed expert and linear form one list (expert, linear, tile), once for every
+// 16 slots of the expert, that the resident workgroups share evenly: a
+// workgroup's start (table entries, slot ids, activations: three dependent round
+// trips) is paid once or twice per call instead of once per 64 rows, no last
+// wave of workgroups is nearly empty, and an expert of many slots is no one's
+// double share (with a loop over its slots in the workgroups that held it, 64
+// experts of 3072 x 2048 at 512 slots took 116 us where one had 17 of them and
+// 175 on skewed routing; now 88 and 85, against 105 on moe_mfma_kernel).
+// A workgroup's waves split K into KW = a.ks parts of NBK 128-code
 // blocks and the tiles into blockDim / 64 / KW sets; D tiles per wave are in
-// flight ahead of the one computed, across the borders of experts.  A pass of
-// 16 slots keeps its activations (MFMA A operand, NBK x 64 bytes per lane) and
-// its t operand in registers, so a tile costs its codes, scales, zeros (lane
-// group g loads those of every fourth part; a shuffle hands them on) and
-// factor row only.  Absent slots of a pass repeat a present one; their rows of
+// flight ahead of the one computed, across the borders of experts.  The slots
+// of a table entry keep their activations (MFMA A operand, NBK x 64 bytes per
+// lane) and their t operand in registers, so a tile costs its codes, scales,
+// zeros (lane group g loads those of every fourth part; a shuffle hands them on)
+// and factor row only.  Absent slots repeat a present one; their rows of
 // the product are not stored.  Codes become the exact integers q - z, each
 // quantization group's partial is scaled in fp32, the rank term is MFMA steps
 // over [t | B_e] with t 2^-e as three fp16 parts that hold all of its 24 bits
 // (e the exponent of the step's largest |t| of the slot, restored in fp32:
-// neither overflow nor fp16's subnormal range is met); the K parts meet in LDS in a fixed order;
-// one rounding.  Two tiles in flight (four layers of 128 experts, 2048 x 768, at
-// 512 slots: 502 us; three 510, one 527) and two workgroups per CU (one: 1.6
-// times the time; 256 registers do not fit three).
+// neither overflow nor fp16's subnormal range is met); the K parts meet in LDS
+// in a fixed order; one rounding.  Two tiles in flight (four layers of 128
+// experts, 2048 x 768, at 512 slots: 502 us; three 510, one 527) and two
+// workgroups per CU (one: 1.6 times the time; 256 registers do not fit three).
 // Where the line lies: NBK <= 4 blocks on KW <= 8 waves keep the activations
 // within 64 registers; groups of 32 codes (four scales per block) were 2 %
 // slower than on the kernels below, and so were few experts or short rows,
@@ -975,7 +986,7 @@ __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves
     // lane i: the table entry of active expert ae0 + i (a share spans few)
     const int elast = (end - 1) / per;
     const int* ent = a.table + kTab * min(ae0 + lane, elast);
-    const int v_e = ent[0], v_sbeg = ent[1], v_scnt = ent[2];
+    const int v_e = ent[0], v_scnt = ent[2];
     int v_rank[kMaxMoeWin];
 #pragma unroll
     for (int i = 0; i < kMaxMoeWin; ++i) v_rank[i] = ent[4 + i];
@@ -1007,22 +1018,19 @@ __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves
 
     // position in the list; the loads run D steps ahead of the arithmetic
     struct Pos {
-        int ae, li, lo, hi, t, p0;
+        int ae, li, lo, hi, t;
     };
     auto enter = [&](Pos& c) {                    // the share's tiles of (ae, li)
         const int base = c.ae * per + (c.li ? a.lin[c.li - 1].blk_end : 0);
         c.lo = max(beg - base, 0);
         c.hi = min(end - base, a.lin[c.li].blk_end - (c.li ? a.lin[c.li - 1].blk_end : 0));
         c.t = c.lo;
-        c.p0 = 0;
     };
     auto over = [&](const Pos& c) { return c.ae > elast; };
-    auto advance = [&](Pos& c) {                  // true: another (ae, li) or pass
+    auto advance = [&](Pos& c) {                  // true: another (ae, li)
         c.t += RW;
         if (c.t < c.hi) return false;
-        c.p0 += 16;
         c.t = c.lo;
-        if (c.p0 < of(v_scnt, c.ae)) return true;
         Pos nx = c;
         do {
             if (++nx.li == a.n) { nx.li = 0; ++nx.ae; }
@@ -1084,12 +1092,11 @@ __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves
                 reinterpret_cast<const u32x4*>(qt + static_cast<uint32_t>(rr * words_row + wo[b])));
     };
 
-    // the pass's slots and activations
+    // the entry's slots and activations
     int sl = 0, osl[4], osl_k = 0;
     u32x4 x[NBK][4];
     auto load_x = [&](const Pos& c) {
-        const int scnt = of(v_scnt, c.ae);
-        sl = c.p0 == 0 ? a.table[kTab * c.ae + 8 + r] : a.sorted[of(v_sbeg, c.ae) + (c.p0 + r < scnt ? c.p0 + r : 0)];
+        sl = a.table[kTab * c.ae + 8 + r];
         const int xrow = a.x_per_slot ? sl : sl / a.k;
         const u32x4* xr = reinterpret_cast<const u32x4*>(a.xp + static_cast<size_t>(xrow) * (K / 2));
 #pragma unroll
@@ -1256,7 +1263,7 @@ __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves
         const int scnt = of(v_scnt, min(cp.ae, elast));
 #pragma unroll
         for (int q = 0; q < QN; ++q) {
-            const bool on = rowv && q0 + q < 4 && cp.p0 + 4 * g + q0 + q < scnt;
+            const bool on = rowv && q0 + q < 4 && 4 * g + q0 + q < scnt;
             const int os = KW == 1 ? osl[q] : KW == 2 ? (kw ? osl[2 + q] : osl[q]) : osl_k;
             if (L.d_out <= kStreamMaxRows)
                 buffer_store_out(L.y, static_cast<uint32_t>(a.T * a.k) * L.d_out, on ? os * L.d_out + row : -1, v[q],
@@ -1264,9 +1271,9 @@ __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves
             else if (on)
                 store_out(L.y, static_cast<size_t>(os) * L.d_out + row, v[q], a.out);
         }
-        const int ae = cp.ae, p0 = cp.p0;
+        const int ae = cp.ae;
         if (live && advance(cp) && !over(cp)) {
-            if (cp.ae != ae || cp.p0 != p0) load_x(cp);
+            if (cp.ae != ae) load_x(cp);
             rank = rank_of(cp.ae, cp.li);
             if (32 * kw < rank) t0 = t_operand(a.lin[cp.li], rank, 32 * kw);
             // wait here, once per segment: x pending where the paths meet
@@ -1580,7 +1587,7 @@ MoeLayout moe_layout(int n, const QW* w, const int* r_max, int E, int T, int k, 
     MoeLayout l;
     l.n_active = 0;
     l.table = 256;
-    l.sorted = l.table + up256(static_cast<size_t>(max_active) * kTab * sizeof(int));
+    l.sorted = l.table + up256(static_cast<size_t>(max_active + S / 16) * kTab * sizeof(int));
     size_t off = l.sorted + up256(static_cast<size_t>(S) * sizeof(int));
     for (int i = 0; i < n; ++i) {
         l.t[i] = off;
@@ -1689,6 +1696,8 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
                              const int32_t* ids, int T, int k, int act, void* const* y, int out, void* ws,
                              hipStream_t st) {
     if (n < 1 || n > kMaxMoeWin) return hipErrorInvalidConfiguration;
+    const int S = T * k;
+    const int max_active = S < E ? S : E;
     const MoeLayout l = moe_layout(n, w, r_max, E, T, k, x_per_slot);
     char* wsb = static_cast<char*>(ws);
     const int d_in = w[0].d_in, bits = w[0].bits;
@@ -1722,8 +1731,6 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
     if (a.ks > 8 || threads > 512 || threads % (64 * a.ks)) return hipErrorInvalidConfiguration;
     if (lg < 64 && a.ks != 1) return hipErrorInvalidConfiguration;
     const int rg_per_block = threads / 64 / a.ks * sets;
-    const int S = T * k;
-    const int max_active = S < E ? S : E;
     // experts meeting two or more slots on average: 4-bit codes go to MFMA
     // (tiles of 16 rows), 2-bit codes are unpacked once per batch
     const bool many = S >= 2 * max_active;
@@ -1732,6 +1739,7 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
     const int nkb = (d_in + 127) / 128;
     const bool stream = bits == 4 && nkb <= 32 && w[0].G % 64 == 0 && max_active >= kStreamMinExperts &&
                         max_active * d_in >= kStreamMinWidth;
+    a.split = stream;
     // Rank rows per preparation workgroup: 16 where that gives most CUs one,
     // fewer where it would leave them idle (a workgroup streams its rows of
     // A_e at one CU's share of the memory rate): 16 experts, 2048 x 768, rank 32:

@@ -544,6 +544,8 @@ def test_gate_up_window_into_gated_down(T, k):
     (1472, 64, 48, 0, 64, 16, 8, False),        # four waves of three, no factors
     (2944, 128, 65, 256, 36, 64, 8, True),      # eight waves of three, 16 slots an expert and more
     (4096, 512, 40, 16, 32, 9, 4, False),       # eight waves of four
+    (2944, 128, 65, 40, 32, 64, 8, True),       # 16 slots an expert on long rows
+    (3072, 128, 40, 16, 40, 60, 8, False),      # between 8 and 16 slots: some experts twice in the list
 ])
 @pytest.mark.parametrize("dyn", [False, True])
 def test_streamed_experts(d_in, G, d_out, r_max, E, T, k, x_per_slot, dyn):
