@@ -84,7 +84,6 @@ constexpr int direct_batches(int lg, int cpl) { return cpl == 2 ? 2 : (lg == 64 
 // the tiles in flight per wave.
 constexpr int kStreamBlocks = 512;
 constexpr int kStreamDepth = 2;
-constexpr int kStreamMinExperts = 32, kStreamMinWidth = 36 << 10;
 constexpr int kStreamMaxRows = (1 << 29) / kMaxSlots - 1;   // 31-bit byte offsets of fp32 outputs
 // Gated calls off the one-launch path form SiLU(g) u in the preparation, once
 // per workgroup that reads the slot, up to this width (128 experts of 768: a
@@ -958,15 +957,11 @@ __device__ __forceinline__ void buffer_store_out(void* y, uint32_t n, int idx, f
 // in a fixed order; one rounding.  Two tiles in flight (four layers of 128
 // experts, 2048 x 768, at 512 slots: 502 us; three 510, one 527) and two
 // workgroups per CU (one: 1.6 times the time; 256 registers do not fit three).
-// Where the line lies: NBK <= 4 blocks on KW <= 8 waves keep the activations
-// within 64 registers; groups of 32 codes (four scales per block) were 2 %
-// slower than on the kernels below, and so were few experts or short rows,
-// where a workgroup's start is not spread over enough tiles (two layers as
-// above with at most 16 experts reached: 84 against 78 us; 64 experts of 512 x
-// 256: 85 against 75).  The rule reads only what the linears of a window
-// share, so a window's outputs equal the single calls'.  gate,up / down of
-// the layer above, traced: 65 / 50 -> 59 / 39 us at 512 slots, 36 / 23 -> 31 /
-// 21 us at 64 (against moe_mfma_kernel and moe_kernel).
+// Where the line lies: see stream_pays (NBK <= 4 blocks on KW <= 8 waves keep the
+// activations within 64 registers; groups of 32 codes, four scales per block,
+// were 2 % slower than on the kernels below).  gate,up / down of the layer above,
+// traced: 65 / 50 -> 59 / 39 us at 512 slots, 36 / 23 -> 31 / 21 us at 64 (against
+// moe_mfma_kernel and moe_kernel).
 template <int NBK, int GPB, int KW, int D>
 __global__ __launch_bounds__(KW > 4 ? 64 * KW : 256) __attribute__((amdgpu_waves_per_eu(2))) void moe_stream_kernel(MoeArgs a) {
     extern __shared__ float red[];                // [2][waves][4][64]
@@ -1670,6 +1665,35 @@ hipError_t launch_stream2(const MoeArgs& a, int blocks, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Whether a linear takes the streamed kernel.  It can where a workgroup's share of
+// K fits (rows of at most 4096 codes in groups of a multiple of 64); it pays
+// where a workgroup's start is spread over enough codes.  Times of captured
+// calls (gate,up windows, single linears and gated calls; 16 to 160 experts, 9 to
+// 512 slots, 512 to 4096 columns, even and skewed routing) against
+// moe_mfma_kernel / moe_kernel:
+//   experts in reach x columns >= 72 K: 0.60 to 1.05 of their time (96 experts
+//   of 768 at 256 slots 0.84 to 0.95, 48 of 1536 0.93 to 0.95, 24 of 4096 0.77 to
+//   0.90; but 24 of 4096 at 64 slots, 1.05 to 1.07).
+//   below it the rows count as well: from 72 M codes in reach 0.80 to 1.02 (64
+//   experts of 768 x 2048, 48 of 768 x 2048), with fewer up to 1.23 (64 of
+//   1024 x 384) and 1.67 (40 of 512 x 192).
+//   fewer than two slots an expert, rows of 1536 and more: 0.59 to 1.0 from 32
+//   experts, 24 on long rows (the other kernel is the VALU's).  Groups of 64,
+//   whose blocks carry two scales: 1.09 at 32 of 2048; on rows of 1024 1.05 to
+//   1.14 with up to 128 experts of 1024 x 2048, 0.80 with 160.
+// It reads one linear at a time, so that a window's outputs equal the single
+// calls' (a window of both kinds goes in two parts).
+bool stream_pays(const QW& w, int S, int experts) {
+    if (w.bits != 4 || w.d_in > 4096 || w.G % 64 || experts < 24) return false;
+    const bool half = w.G % 128 != 0, few = S < 2 * experts;
+    const long long codes = static_cast<long long>(experts) * w.d_in * w.d_out;
+    if (half && few && w.d_in > 768 && w.d_in < 1536) return codes >= 240 << 20;
+    if (experts < 32 && !few && S < 5 * experts) return false;
+    if (experts * w.d_in >= 72 << 10) return true;
+    if (few && w.d_in >= 1536 && experts >= (half ? 40 : w.d_in >= 3072 ? 24 : 32)) return true;
+    return experts >= 32 && codes >= 72 << 20;
+}
+
 // Rows of nkb 128-code blocks: the fewest waves that leave each at most four.
 hipError_t launch_stream(const MoeArgs& a, int nkb, int blocks, hipStream_t st) {
     if (nkb > 16) return nkb <= 24 ? launch_stream2<3, 8>(a, blocks, st) : launch_stream2<4, 8>(a, blocks, st);
@@ -1698,6 +1722,29 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
     if (n < 1 || n > kMaxMoeWin) return hipErrorInvalidConfiguration;
     const int S = T * k;
     const int max_active = S < E ? S : E;
+    // on or off the streamed kernel: a window of both kinds goes in two parts,
+    // one after the other in the same workspace
+    const bool stream = stream_pays(w[0], S, max_active);
+    for (int other = 1; other < n; ++other) {
+        if (stream_pays(w[other], S, max_active) == stream) continue;
+        for (const bool part : {stream, !stream}) {
+            QW pw[kMaxMoeWin];
+            const uint16_t *pA[kMaxMoeWin], *pB[kMaxMoeWin];
+            const int32_t *pr[kMaxMoeWin], *ps[kMaxMoeWin];
+            int pm[kMaxMoeWin], m = 0;
+            void* py[kMaxMoeWin];
+            for (int i = 0; i < n; ++i) {
+                if (stream_pays(w[i], S, max_active) != part) continue;
+                pw[m] = w[i]; pA[m] = A[i]; pB[m] = B[i]; pm[m] = r_max[i]; pr[m] = ranks[i];
+                ps[m] = slot_ranks ? slot_ranks[i] : nullptr;
+                py[m++] = y[i];
+            }
+            const hipError_t e = launch_moe_decode(m, pw, pA, pB, pm, pr, slot_ranks ? ps : nullptr, E, x, u,
+                                                   x_per_slot, ids, T, k, act, py, out, ws, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     const MoeLayout l = moe_layout(n, w, r_max, E, T, k, x_per_slot);
     char* wsb = static_cast<char*>(ws);
     const int d_in = w[0].d_in, bits = w[0].bits;
@@ -1735,10 +1782,7 @@ hipError_t launch_moe_decode(int n, const QW* w, const uint16_t* const* A, const
     // (tiles of 16 rows), 2-bit codes are unpacked once per batch
     const bool many = S >= 2 * max_active;
     const bool on_mfma = many && bits == 4;
-    // the streamed kernel: see its comment for where the line lies
     const int nkb = (d_in + 127) / 128;
-    const bool stream = bits == 4 && nkb <= 32 && w[0].G % 64 == 0 && max_active >= kStreamMinExperts &&
-                        max_active * d_in >= kStreamMinWidth;
     a.split = stream;
     // Rank rows per preparation workgroup: 16 where that gives most CUs one,
     // fewer where it would leave them idle (a workgroup streams its rows of

@@ -288,6 +288,26 @@ def test_window_equals_singles_bitwise(T, x_per_slot):
         assert torch.equal(y, y2)
 
 
+@pytest.mark.parametrize("T", [8, 64])
+@pytest.mark.parametrize("dyn", [False, True])
+def test_window_on_both_sides_of_the_streamed_rule_equals_singles_bitwise(T, dyn):
+    """64 experts of 1024 columns with few rows (not streamed) and with many
+    (streamed) in one window: each linear exactly its single-call result."""
+    E, d_in, k = 64, 1024, 8
+    exs = [_random_experts(E, d_out, d_in, r_max, 50 + d_out) for d_out, r_max in ((96, 16), (1200, 8), (80, 0), (1216, 24))]
+    ids = torch.from_numpy(wl.routing(T, 54, 0, E, k)[0]).cuda()
+    x = torch.from_numpy(wl.activation((T, d_in), 54, 0, 1).bits.view(np.int16)).view(torch.float16).cuda()
+    g = torch.Generator(device="cuda").manual_seed(5)
+    sr = None
+    if dyn:
+        sr = [torch.randint(0, ex.r_max + 1, (T, k), dtype=torch.int32, device="cuda", generator=g) for ex in exs]
+        sr[1] = None
+    ys = cl.moe_linear_decode_window(exs, x, ids, slot_ranks=sr)
+    for i, (ex, y) in enumerate(zip(exs, ys)):
+        one = cl.moe_linear_decode_window([ex], x, ids, slot_ranks=None if sr is None else [sr[i]])[0]
+        assert torch.equal(y, one), i
+
+
 def test_window_matches_oracle():
     E, d_in, bits, G, k, T = 12, 512, 4, 128, 3, 5
     exs, host = [], []
@@ -544,15 +564,22 @@ def test_gate_up_window_into_gated_down(T, k):
     (1472, 64, 48, 0, 64, 16, 8, False),        # four waves of three, no factors
     (2944, 128, 65, 256, 36, 64, 8, True),      # eight waves of three, 16 slots an expert and more
     (4096, 512, 40, 16, 32, 9, 4, False),       # eight waves of four
+    (256, 128, 60, 8, 300, 40, 8, False),       # the narrow ones from 72 K columns of experts on: two blocks a wave
+    (512, 256, 33, 20, 150, 20, 8, True),       # one wave of four
+    (768, 64, 50, 40, 100, 13, 8, True),        # two waves of three, two groups per block
+    (832, 64, 16, 72, 90, 64, 8, False),        # a half block at the end
     (2944, 128, 65, 40, 32, 64, 8, True),       # 16 slots an expert on long rows
+    (1536, 64, 40, 16, 44, 11, 4, False),       # fewer than two slots an expert
     (3072, 128, 40, 16, 40, 60, 8, False),      # between 8 and 16 slots: some experts twice in the list
+    (4096, 128, 40, 16, 26, 16, 5, False),      # a few experts of some slots: the other MFMA kernel
+    (1024, 64, 40, 16, 80, 16, 8, False),       # rows of 1024 in groups of 64, few slots: the VALU kernel
 ])
 @pytest.mark.parametrize("dyn", [False, True])
 def test_streamed_experts(d_in, G, d_out, r_max, E, T, k, x_per_slot, dyn):
-    """The streamed kernel at the edges of its instances: ragged row tiles,
-    partial K blocks, every number of K waves, ranks off 8 and past one step,
-    one slot, several and several passes of 16 slots on an expert, an expert
-    id out of range, per-slot ranks."""
+    """The streamed kernel at the edges of its instances and the calls on the
+    other side of its rule: ragged row tiles, partial K blocks, every number of
+    K waves, ranks off 8 and past one step, one slot, several and several
+    passes of 16 slots on an expert, an expert id out of range, per-slot ranks."""
     Q, s, z, A, B = _oracle_experts(E, d_out, d_in, 4, G, r_max, 60 + d_in, svd=False)
     ranks = wl.moe_expert_ranks(60, 0, 0, E, levels=sorted({0, r_max // 3, r_max})) if r_max else np.zeros(E, np.int32)
     ids, wts = wl.routing(T, 61, 0, E, k)
@@ -582,7 +609,7 @@ def test_streamed_experts(d_in, G, d_out, r_max, E, T, k, x_per_slot, dyn):
                 ref[t, j] = W @ X[t, j] + B[e][:, :r].astype(np.float64) @ (A[e][:r].astype(np.float64) @ X[t, j])
     with pytest.raises(cl.ClError):
         cl.moe_status()
-    # fp32 sums of d_in products and r_max factor terms, t to 2^-22
+    # fp32 sums of d_in products and r_max factor terms, t to 2^-22 or better
     assert rel_l2(got, ref) <= 2.0 ** -22 + 2.0 ** -24 * np.sqrt(d_in)
 
 
@@ -590,7 +617,7 @@ def test_streamed_experts_keep_large_and_small_factor_products():
     """t = A x beyond fp16's largest value (one token) and far below its
     subnormal range (another): the streamed kernel scales each slot's t by a
     power of two."""
-    E, T, k, d_in, d_out, r_max = 40, 8, 8, 1024, 48, 16
+    E, T, k, d_in, d_out, r_max = 40, 8, 8, 2048, 48, 16
     Q, s, z, A, B = _oracle_experts(E, d_out, d_in, 4, 128, r_max, 70, svd=False)
     A = (A.astype(np.float64) * 5e4).astype(np.float16)
     ids, _ = wl.routing(T, 71, 0, E, k)
