@@ -648,17 +648,22 @@ int prefill_cus() {
 // 14336 x 4096 at M = 64 / 128 / 200 / 333: 56.2 58.8 60.6 75.9, 38.8 41.2 57.2
 // 79.9, 37.4 38.4 67.2 95.7, 29.1 45.9 82.4 119.  So: the smallest tile while
 // one of them per CU holds the problem, then 128 x 64, then 64 x 128 up to two
-// per CU.
+// per CU.  The same holds at short K, where a set has one or two steps (4096
+// rows at M = 64 / 333 / 768: K = 512 22.7 25.9 26.9 -> 16.2 19.5 24.5 us, K = 1024
+// 26.7 30.7 32.2 -> 17.1 22.5 28.6), and at long K but for 2 and 3 bits, whose
+// dequantization costs more than the second half of the chip gives from 1.5
+// tiles of 64 x 128 per CU on (4096 x 14336 at M = 768 / 1024, 3 bits: 172 177 ->
+// 163 184; 8192 x 8192 at M = 400 / 512: 97 97 -> 101 102).
 struct PrefillTile {
     int jt, mt, ks;
 };
 
-PrefillTile prefill_tile(int M, int N) {
+PrefillTile prefill_tile(int M, int N, int K, int bits) {
     auto tiles = [&](int m, int n) { return static_cast<long long>((M + m - 1) / m) * ((N + n - 1) / n); };
     const int cus = prefill_cus();
     if (tiles(64, 64) <= cus) return {1, 4, 4};
     if (tiles(128, 64) <= cus) return {1, 8, 2};
-    if (tiles(64, 128) <= 2 * cus) return {2, 4, 2};
+    if (tiles(64, 128) <= (bits != 4 && K >= 8192 ? 3 * cus / 2 : 2 * cus)) return {2, 4, 2};
     return tiles(128, 256) < 2 * cus ? PrefillTile{2, 8, 1} : PrefillTile{4, 8, 1};
 }
 
@@ -705,7 +710,7 @@ hipError_t launch_linear_prefill(const QW& w, const LR& c, const void* X, int M,
     a.M = M; a.N = w.d_out; a.K = w.d_in; a.G = w.G;
     a.rank = c.rank; a.r_max = c.r_max; a.r_pad = (c.rank + 31) / 32 * 32;
     a.out = out;
-    const PrefillTile t = prefill_tile(M, w.d_out);
+    const PrefillTile t = prefill_tile(M, w.d_out, w.d_in, w.bits);
     a.mblocks = (M + 16 * t.mt - 1) / (16 * t.mt);
     const uint16_t* Xa = static_cast<const uint16_t*>(X);
     if (c.rank > 0) {

@@ -250,3 +250,18 @@ def test_prefill_every_tile(M, d_out, bits, G, d_in):
     ref = linear.forward_packed(Q, s, z, bits, G, A, B, 33, x.values)
     W_hat = quant.dequant_packed(Q, s, z, bits, G, d_in)
     assert_oracle(out_to_numpy(y), ref, extra=fp16_tile_bound(W_hat, x.values, A, B, 33))
+
+
+@pytest.mark.parametrize("bits,G,M,d_out", [(3, 128, 400, 6000), (3, 128, 450, 6500), (2, 64, 450, 6500)])
+def test_prefill_long_rows_of_narrow_codes(bits, G, M, d_out):
+    """Rows of 8192 codes on each side of one and a half 64 x 128 tiles per CU:
+    two K sets, then 128 x 128 tiles."""
+    d_in = 8192
+    w, (Q, s, z, A, B) = _layer(d_out, d_in, bits, G, 8, M + bits)
+    c = cl.LowRank(dev_f16(A), dev_f16(B), 8, 5)
+    x = wl.activation((M, d_in), 25, M, d_out)
+    y = cl.linear_prefill(w, c, dev_u16(x.bits, torch.float16), out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = linear.forward_packed(Q, s, z, bits, G, A, B, 5, x.values)
+    W_hat = quant.dequant_packed(Q, s, z, bits, G, d_in)
+    assert_oracle(out_to_numpy(y), ref, extra=fp16_tile_bound(W_hat, x.values, A, B, 5))
