@@ -231,9 +231,9 @@ __device__ __forceinline__ double recip_f64(double q) {
 // written once per step.  A thread owns the same CPT columns throughout (v, w
 // and the new v stay in its registers) and R rows at a time; the first R
 // rows' loads are issued before the reductions.  Row i always belongs to
-// workgroup i mod grid.  Bound by the chain of one launch (two reductions; 4.4
-// us a step at <= 256 columns, 6.3 at 1024) up to n ~ 2000, beyond by the 16
-// n^2 bytes.  The whole call at 1024 x 4096, r_max 128: 134 -> 7.4 ms, 4096 x
+// workgroup i mod grid.  Bound by the chain of one launch (two reductions; 4.0
+// us a step at <= 256 columns, 6.5 at 1024) up to n ~ 2000, beyond by the 16
+// n^2 bytes.  The whole call at 1024 x 4096, r_max 128: 134 -> 7.5 ms, 4096 x
 // 4096: 4.9 -> 0.11 s, against cyclic Jacobi (10 to 18 sweeps of n - 1 rounds
 // of two launches over C and X).
 template <int CPT, int R>
@@ -353,9 +353,9 @@ __global__ __launch_bounds__(256) void householder_step_kernel(double* __restric
 __global__ __launch_bounds__(256) void tridiagonal_prep_kernel(const double* __restrict__ d, double* __restrict__ e,
                                                                int n, double2* __restrict__ de,
                                                                int2* __restrict__ blk, double* __restrict__ bounds) {
-    __shared__ double lo[256], hi[256], em[256];
-    __shared__ int first[256], last[256], odd[256];
-    const int tid = threadIdx.x, per = (n + 255) / 256;
+    __shared__ double red[3][4];
+    __shared__ int edge[3][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, per = (n + 255) / 256;
     const int i0 = min(tid * per, n), i1 = min(i0 + per, n);
     const double tol = kDrop * sqrt(static_cast<double>(n));
     for (int i = i0; i < i1; ++i)
@@ -377,12 +377,33 @@ __global__ __launch_bounds__(256) void tridiagonal_prep_kernel(const double* __r
             t = i;
         }
     }
-    lo[tid] = l; hi[tid] = h; em[tid] = m;
-    first[tid] = f; last[tid] = t; odd[tid] = bad;
+    // the last start at or before this thread's rows, the first one after them
+    int beg = t, end = f;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int p = __shfl_up(beg, off, 64), q = __shfl_down(end, off, 64);
+        if (lane >= off) beg = max(beg, p);
+        if (lane + off < 64) end = min(end, q);
+        l = fmin(l, __shfl_xor(l, off, 64));
+        h = fmax(h, __shfl_xor(h, off, 64));
+        m = fmax(m, __shfl_xor(m, off, 64));
+        bad |= __shfl_xor(bad, off, 64);
+    }
+    if (lane == 63) edge[0][wave] = beg;
+    if (lane == 0) {
+        edge[1][wave] = end;
+        edge[2][wave] = bad;
+        red[0][wave] = l; red[1][wave] = h; red[2][wave] = m;
+    }
     __syncthreads();
-    int beg = 0, end = n;
-    for (int u = 0; u < tid; ++u) beg = max(beg, last[u]);
-    for (int u = tid + 1; u < 256; ++u) end = min(end, first[u]);
+    beg = __shfl_up(beg, 1, 64);
+    end = __shfl_down(end, 1, 64);
+    if (lane == 0) beg = 0;
+    if (lane == 63) end = n;
+    for (int w = 0; w < 4; ++w) {
+        if (w < wave) beg = max(beg, edge[0][w]);
+        if (w > wave) end = min(end, edge[1][w]);
+    }
     for (int i = i0; i < i1; ++i) {
         if (starts(i)) beg = i;
         blk[i].x = beg;
@@ -391,24 +412,20 @@ __global__ __launch_bounds__(256) void tridiagonal_prep_kernel(const double* __r
         blk[i].y = end;
         if (starts(i)) end = i;
     }
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s) {
-            lo[tid] = fmin(lo[tid], lo[tid + s]);
-            hi[tid] = fmax(hi[tid], hi[tid + s]);
-            em[tid] = fmax(em[tid], em[tid + s]);
-            odd[tid] |= odd[tid + s];
-        }
-        __syncthreads();
-    }
     if (tid == 0) {
-        const double norm = fmax(fabs(lo[0]), fabs(hi[0]));
+        for (int w = 1; w < 4; ++w) {
+            l = fmin(l, red[0][w]);
+            h = fmax(h, red[1][w]);
+            m = fmax(m, red[2][w]);
+            bad |= edge[2][w];
+        }
+        const double norm = fmax(fabs(l), fabs(h));
         const double pad = 4e-16 * norm * sqrt(static_cast<double>(n));
-        bounds[0] = lo[0] - pad;
-        bounds[1] = hi[0] + pad;
+        bounds[0] = l - pad;
+        bounds[1] = h + pad;
         bounds[2] = norm;
-        bounds[3] = 2.3e-308 * fmax(1.0, em[0]);
-        bounds[4] = odd[0];
+        bounds[3] = 2.3e-308 * fmax(1.0, m);
+        bounds[4] = bad;
         bounds[5] = 0.0;
     }
 }
@@ -665,16 +682,20 @@ __global__ __launch_bounds__(256) void orthogonalise_kernel(const double* __rest
 }
 
 // bounds[5] = the worst of vector j's |T z - lambda z| / |T| and of its inner
-// products Gm[j][k] with the others, each over its tolerance (products with
-// vectors of eigenvalue zero apart); 1e300 where one is not a number.  Gm is
-// left as (3 I - Gm) / 2: Z times it is orthonormal to the square of Z's own
-// error, 1e-9 to 1e-18 (one step of Newton's iteration for the polar factor).
-// One workgroup per vector; the bits of a positive double are in its order.
+// products with the others, each over its tolerance (products with vectors of
+// eigenvalue zero apart); 1e300 where one is not a number.  Row j of M = (3 I -
+// Z^T Z) / 2: Z M is orthonormal to the square of Z's own error, 1e-9 to 1e-18
+// (one step of Newton's iteration for the polar factor).  One workgroup per
+// vector; a thread sums every parts-th row of one other's product, a wave's
+// threads along a row of Z.  The bits of a positive double are in its order.
+// Bound by the chain of its loads, 16 at a time: 128 vectors of 1024, 44 us (the
+// products on the matrix cores, four workgroups for want of tiles, and the check
+// in a launch of its own 62 + 13 us).
 __global__ __launch_bounds__(256) void check_kernel(const double* __restrict__ d, const double* __restrict__ e, int n,
                                                     const double* __restrict__ lam, int r_max,
-                                                    const double* __restrict__ Z, double* __restrict__ Gm,
+                                                    const double* __restrict__ Z, double* __restrict__ M,
                                                     double* __restrict__ bounds) {
-    __shared__ double red[4];
+    __shared__ double red[4], part[256];
     const int j = blockIdx.x, tid = threadIdx.x;
     const double norm = bounds[2] > 0.0 ? bounds[2] : 1.0, l = lam[j];
     auto z = [&](int i) { return Z[static_cast<size_t>(i) * r_max + j]; };
@@ -687,11 +708,19 @@ __global__ __launch_bounds__(256) void check_kernel(const double* __restrict__ d
     }
     ss = block_sum_f64(ss, red);
     double worst = sqrt(ss) / (norm * kResidualTol);
+    const int parts = 256 / r_max, k = tid % r_max, p = tid / r_max;
+    double g = 0.0;
+    if (p < parts) {
+#pragma unroll 16
+        for (int i = p; i < n; i += parts) g = fma(z(i), Z[static_cast<size_t>(i) * r_max + k], g);
+    }
+    part[tid] = g;
+    __syncthreads();
     if (tid < r_max) {
-        double* g = Gm + static_cast<size_t>(j) * r_max + tid;
+        for (int u = 1; u < parts; ++u) g += part[u * r_max + tid];
         const double one = tid == j ? 1.0 : 0.0;
-        const double off = tid == j || (l > 0.0 && lam[tid] > 0.0) ? *g - one : 0.0;
-        *g = fma(-0.5, off, one);
+        const double off = tid == j || (l > 0.0 && lam[tid] > 0.0) ? g - one : 0.0;
+        M[static_cast<size_t>(j) * r_max + tid] = fma(-0.5, off, one);
         const double o = fabs(off) / kOrthogonalTol;
         worst = o <= worst ? worst : o;
     }
@@ -885,7 +914,7 @@ hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uin
     do {
         // C is free now: the eliminations of n / 4 vectors at a time (4 planes
         // of n each); the iterates in P until the product with E needs it, the
-        // finished ones row by row, then their products, in Xr; the
+        // finished ones row by row, then the check's M, in Xr; the
         // orthonormal ones in C
         const int batch = n < 4 ? 1 : n / 4, until = sweeps == 0 ? kInverseSweeps : sweeps + 1;
         for (; r_max > 0 && sweeps < until; ++sweeps) {
@@ -900,7 +929,6 @@ hipError_t launch_build_compensation(const float* W, const QW& w, int r_max, uin
             });
         }
         if (r_max > 0) {
-            gemm<false, false>(P, 1, r_max, P, 1, r_max, r_max, r_max, n, Xr, r_max, st);
             hipLaunchKernelGGL(check_kernel, dim3(r_max), dim3(256), 0, st, d, e, n, lam, r_max, P, Xr, bounds);
             gemm<true, false>(P, r_max, 1, Xr, 1, r_max, n, r_max, r_max, C, r_max, st);
             by_columns(n, [&](auto cpt) {
