@@ -16,14 +16,16 @@
 //    routing table -- so no workgroup ever waits for another -- counts slots
 //    per expert, scans the counts and takes e = the j-th routed expert in
 //    ascending id order (none: it exits).  It computes t[slot][i] =
-//    A_e[i] . x_slot for the rank rows i = 16q .. 16q + 15 of its linear over
+//    A_e[i] . x_slot for the rank rows i = 16q .. 16q + 15 (8 or 4 rows where
+//    16 would leave CUs without a workgroup) of its linear over
 //    all of e's slots on MFMA, 16 slots per pass, its four waves splitting K.
 //    Bound by its chain (routing tables, then two rounds of loads): fewer,
 //    larger workgroups (one rank row per wave before) take 17.0 -> 12.9 us at
 //    512 slots over 128 experts of 2048 x 768, two linears of rank <= 32.  A
 //    gated call forms SiLU(g) u as it reads the activations.  Workgroup
-//    (0, j, 0) also writes entry j of the active-expert table and e's slots,
-//    in slot order, into the sorted slot list, and (linear, j, 0) that
+//    (0, j, 0) also writes e's entry of the active-expert table (for the
+//    streamed kernel one for every 16 of its slots) and e's slots, in slot
+//    order, into the sorted slot list, and (linear, j, 0) that
 //    linear's rank of e; workgroups (linear, 0, 0) write the number of
 //    routed experts and zero rows for slots whose id is out of range.  The
 //    remaining workgroups prepare the activations (fp16, pair-permuted,
@@ -71,15 +73,6 @@ constexpr int kMaxMoeWin = 4;        // linears per window
 // waves)
 constexpr int kDirectMaxSlots = 8;
 constexpr int direct_batches(int lg, int cpl) { return cpl == 2 ? 2 : (lg == 64 ? 4 : 2); }
-// MFMA path: 16-row tiles per workgroup and K blocks in flight per wave.
-// Measured on the 48-layer T = 64 step with the workgroup's loads issued in
-// need order (scales and zeros, slot ids, code blocks): 8 x 1 166 us per
-// layer, 4 x 2 191, 8 x 2 229, 12 x 1 230, 16 x 1 227 (with the code loads
-// issued after the scale/zero copy: 4 x 2 213 us; one tile of 16 rows had
-// taken 389, every workgroup re-reading its slots' activations).  Once the
-// pipeline's tail stopped re-reading code blocks: 4 x 1 143.7 us, 8 x 1
-// 150.5, 2 x 1 153.0, 6 x 1 161.7, 4 x 2 ~160 (165 VGPRs at 4 x 1: three
-// waves per SIMD against two).
 // Streamed path: workgroups of 4 waves that share the tiles (two per CU), and
 // the tiles in flight per wave.
 constexpr int kStreamBlocks = 512;
@@ -91,6 +84,15 @@ constexpr int kStreamMaxRows = (1 << 29) / kMaxSlots - 1;   // 31-bit byte offse
 // exponentials cost as much as that launch (16 experts of 1536: 10.8 against
 // 5.9 + 4.5 us).
 constexpr int kGateFuseMaxWidth = 1024;
+// MFMA path: 16-row tiles per workgroup and K blocks in flight per wave.
+// Measured on the 48-layer T = 64 step with the workgroup's loads issued in
+// need order (scales and zeros, slot ids, code blocks): 8 x 1 166 us per
+// layer, 4 x 2 191, 8 x 2 229, 12 x 1 230, 16 x 1 227 (with the code loads
+// issued after the scale/zero copy: 4 x 2 213 us; one tile of 16 rows had
+// taken 389, every workgroup re-reading its slots' activations).  Once the
+// pipeline's tail stopped re-reading code blocks: 4 x 1 143.7 us, 8 x 1
+// 150.5, 2 x 1 153.0, 6 x 1 161.7, 4 x 2 ~160 (165 VGPRs at 4 x 1: three
+// waves per SIMD against two).
 constexpr int kMoeTpw = 4;
 constexpr int kMoeNbuf = 1;
 

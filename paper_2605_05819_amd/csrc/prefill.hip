@@ -16,9 +16,10 @@
 //     ones, with K split between the waves of a workgroup, where those would
 //     leave CUs idle: see prefill_tile), K in steps of 128 codes.  X' tiles
 //     go from global memory straight into LDS (global_load_lds, 16 bytes per
-//     lane, two 32 KB stages, chunks XOR-swizzled by row so the MFMA operand
-//     reads are bank-conflict free).  Each of the four waves owns 128 tokens
-//     x 16 JT weight rows (8 x JT MFMA tiles): it loads its rows' packed
+//     lane, two stages of 256 bytes per token, chunks XOR-swizzled by row so
+//     the MFMA operand reads are bank-conflict free).  Each of the four waves
+//     of a set owns 16 MT tokens x 16 JT weight rows (MT x JT MFMA tiles, MT =
+//     8 or 4) over its set's K steps: it loads its rows' packed
 //     codes for the next K step into registers (one 16-byte load per lane
 //     and fragment: 32 codes of one quantization group, so one scale and zero
 //     per lane) and dequantizes them as s * (q - z) in fp16 (the integer
@@ -39,7 +40,7 @@
 //     32 rows per wave it ran 401 us on 14336 x 4096 (X' operand reads at
 //     512 bytes of LDS per MFMA, one wave per SIMD to hide latency), and 64
 //     rows per wave need more than the 512 registers a lane can hold.
-//  Workgroups are numbered so that the N tiles of one 128-token block run on
+//  Workgroups are numbered so that the N tiles of one token block run on
 //  one XCD (workgroup i runs on XCD i mod 8) and share its L2 copy of X'.
 
 #include "cl_device.h"
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(256 * KS, 2) void prefill_kernel(PrefillArgs a) {
     // on its own run of K steps
     constexpr int BM = 16 * MT;
     constexpr int BNT = 64 * JT;
-    // LDS (dynamic, prefill_lds_bytes): two stages of X', [BM rows][16
+    // LDS (dynamic, prefill_set_lds units a set): two stages of X', [BM rows][16
     // chunks of 8 k], chunk c of row r stored at slot c ^ xswz(r & 15); then
     // the scales and zeros of the workgroup's BNT rows, windows of 8
     // consecutive groups, double-buffered: [buffer][scale, zero][group][row]

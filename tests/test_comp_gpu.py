@@ -191,7 +191,7 @@ def test_full_size_4096_rank_128_against_lapack(capsys):
     one to 1e-6 sigma_0; the residual energy of the fp16 factors at rank 128
     equals the tail energy sum_{j>128} sigma_j^2 from above (Eckart-Young-
     Mirsky: no rank-128 matrix does better) within 1e-4 of it.  Reports the
-    call's time and its Jacobi sweeps."""
+    call's time and its sweeps over the vectors."""
     import time
     n, r_max = 4096, 128
     W = wl.weight((n, n), 51, 0, 0)
@@ -215,7 +215,7 @@ def test_full_size_4096_rank_128_against_lapack(capsys):
     assert 1.0 - 1e-9 <= ratio <= 1.0 + 1e-4, ratio
     assert sweeps == 2                            # an ordinary residual passes its first check
     with capsys.disabled():
-        print("\n[cl_build_compensation 4096 x 4096, r_max 128: %.2f s, %d Jacobi sweeps, residual/tail %.8f]"
+        print("\n[cl_build_compensation 4096 x 4096, r_max 128: %.2f s, %d sweeps, residual/tail %.8f]"
               % (dt, sweeps, ratio))
 
 
@@ -343,8 +343,8 @@ def test_equal_singular_values_in_one_run(n, big, r_max):
 @pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
 @pytest.mark.parametrize("n,big,r_max", [(64, 128, 8), (300, 384, 0), (200, 128, 16)])
 def test_a_residual_that_is_not_finite_is_an_error(value, n, big, r_max):
-    """An error with A and B as they were, and the next call is not affected;
-    the sweeps reported are the calls' own."""
+    """An error, and the next call is not affected; the sweeps reported are the
+    calls' own."""
     E = np.random.default_rng(n).standard_normal((n, big)).astype(np.float32)
     _build(E, r_max)
     assert cl.build_compensation_sweeps() == (2 if r_max else 1)
