@@ -341,18 +341,14 @@ __global__ __launch_bounds__(256) void moe_prep_kernel(MoeArgs a) {
                     if constexpr (GATED) uv[v] = *reinterpret_cast<const u32x4*>(ur + k);
                 }
                 __builtin_amdgcn_sched_barrier(0);   // all loads out before any is converted
-                if (!GATED && a.act != DT_FP16) {
+                auto products = [&](auto x8) {
 #pragma unroll
-                    for (int v = 0; v < UN; ++v) xv[v] = act8_to_f16(xv[v], a.act);
-                }
-#pragma unroll
-                for (int v = 0; v < UN; ++v) {
-                    if (sb + v < s1) {
-                        u32x4 x8 = xv[v];
-                        if constexpr (GATED) x8 = gated8_to_f16(xv[v], uv[v], a.act);
-                        acc[v & 3] = mfma(x8, av[v], acc[v & 3]);
-                    }
-                }
+                    for (int v = 0; v < UN; ++v)
+                        if (sb + v < s1) acc[v & 3] = mfma(x8(v), av[v], acc[v & 3]);
+                };
+                if constexpr (GATED) products([&](int v) { return gated8_to_f16(xv[v], uv[v], a.act); });
+                else if (a.act == DT_FP16) products([&](int v) { return xv[v]; });
+                else products([&](int v) { return act8_to_f16(xv[v], DT_BF16); });
             }
             tred[wave][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
             __syncthreads();
